@@ -295,7 +295,7 @@ struct Impl final : ImplBase {
     }
     // x-pass workgroups per member, largest over the tile variants (sizes the
     // partial-sum buffer)
-    int nwg_x() const override { return (int)(N2 / rows_x(NX, sizeof(cx<T>), NVARIANT - 1)); }
+    int nwg_x() const override { return (int)(N2 / xpass_wg_rows<T, NX, N>(NVARIANT - 1)); }
     static size_t field_bytes() { return (size_t)M * Qp * sizeof(CX); }
     size_t state_bytes() const override { return STATE_HDR_BYTES + 6 * ((field_bytes() + 255) / 256 * 256); }
 
@@ -429,7 +429,7 @@ struct Impl final : ImplBase {
     template <int V>
     static constexpr int nby(int nf) { return (N * KP + cols_of(N, V) - 1) / cols_of(N, V) * nf; }
     template <int V>
-    static constexpr int nwg(int) { return (int)(N2 / rows_x(NX, sizeof(cx<T>), V)); }
+    static constexpr int nwg(int) { return (int)(N2 / xpass_wg_rows<T, NX, N>(V)); }
     static constexpr int NBZ = (Q + CZ - 1) / CZ;  // z-pass tiles per member
     static int nwg_of(int v) { return v == 2 ? nwg<2>(0) : (v == 1 ? nwg<1>(0) : nwg<0>(0)); }
 
@@ -473,11 +473,11 @@ struct Impl final : ImplBase {
         const CX* w = static_cast<const CX*>(g.twx);
         constexpr int nw = nwg<V>(0);
         const int* n = g.n_nc[SP ? 1 : 0];
-        if (n[0]) k_xpass<T, NX, N, 0, V, SP><<<(unsigned)(nw * n[0]), xpass_threads<T, NX, V, SP>(), 0, g.stream>>>(mt, w);
+        if (n[0]) k_xpass<T, NX, N, 0, V, SP><<<(unsigned)(nw * n[0]), xpass_block<T, NX, N, 0, V, SP>(), 0, g.stream>>>(mt, w);
         mt += n[0];
-        if (n[1]) k_xpass<T, NX, N, 1, V, SP><<<(unsigned)(nw * n[1]), xpass_threads<T, NX, V, SP>(), 0, g.stream>>>(mt, w);
+        if (n[1]) k_xpass<T, NX, N, 1, V, SP><<<(unsigned)(nw * n[1]), xpass_block<T, NX, N, 1, V, SP>(), 0, g.stream>>>(mt, w);
         mt += n[1];
-        if (n[2]) k_xpass<T, NX, N, 3, V, SP><<<(unsigned)(nw * n[2]), xpass_threads<T, NX, V, SP>(), 0, g.stream>>>(mt, w);
+        if (n[2]) k_xpass<T, NX, N, 3, V, SP><<<(unsigned)(nw * n[2]), xpass_block<T, NX, N, 3, V, SP>(), 0, g.stream>>>(mt, w);
         return mt + n[2];
     }
     template <int V>

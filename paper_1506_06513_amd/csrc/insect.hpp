@@ -587,12 +587,6 @@ __device__ inline void kin_cast_rest(const Kin& a, KinT<TM>& b) {
 }
 
 template <typename TM>
-__device__ inline void kin_cast(const Kin& a, KinT<TM>& b) {
-    kin_cast_arrays(a, b, 0, 1);
-    kin_cast_rest(a, b);
-}
-
-template <typename TM>
 __device__ __forceinline__ TM chi_of(TM delta, const KinT<TM>& k) {
     if (k.smooth == FLUSI_SMOOTH_TANH) return TM(0.5) * (TM(1) - tanh(delta / k.h));
     if (delta <= -k.h) return TM(1);
@@ -650,9 +644,13 @@ __device__ __attribute__((noinline)) TM table_radius(const TM* tab, TM ex, TM ey
     return (TM(1) - f) * tab[j] + f * tab[j + 1];
 }
 
+// Keeps the reads of one part's constants (in LDS) from being moved ahead of the
+// part before: all parts' at once would cost the callers their registers.
+__device__ __forceinline__ void mask_stage() { __asm__ volatile("" ::: "memory"); }
+
 // chi of each part (body, left wing, right wing; 0 where absent or culled) and
 // the body-frame coordinates of the point.
-template <typename TM>
+template <bool WINGS = true, typename TM>
 __device__ __forceinline__ void part_chis(const KinT<TM>& k, TM x, TM y, TM z, TM (&c)[3], TM (&xb)[3]) {
     c[0] = c[1] = c[2] = TM(0);
     const TM rel[3] = {x - k.xc[0], y - k.xc[1], z - k.xc[2]};
@@ -677,8 +675,10 @@ __device__ __forceinline__ void part_chis(const KinT<TM>& k, TM x, TM y, TM z, T
         }
         c[0] = chi_of(d, k);
     }
-    if (k.wings) {
+    if (WINGS && k.wings) {
+#pragma unroll 1
         for (int s = 0; s < 2; ++s) {
+            mask_stage();
             const TM g0 = x - k.wc[s][0], g1 = y - k.wc[s][1], g2 = z - k.wc[s][2];
             if (g0 * g0 + g1 * g1 + g2 * g2 > k.r2w) continue;  // outside the wing's cull sphere: chi == 0
             const TM d0[3] = {xb[0] - k.piv[s][0], xb[1] - k.piv[s][1], xb[2] - k.piv[s][2]};
@@ -719,10 +719,8 @@ __device__ __forceinline__ int part_of_max(const TV (&c)[3]) {
     return part;
 }
 
-// Part choice in FP64 at a point where two parts overlap.  Out of line: the
-// FP64 geometry is rare and would otherwise set the register count of the
-// FP32 kernels that call eval_mask.
-__device__ __attribute__((noinline)) int part_of_max64(const KinT<double>* k64, double x, double y, double z) {
+// Part choice in FP64 at a point where two parts overlap.
+__device__ __forceinline__ int part_of_max64(const KinT<double>* k64, double x, double y, double z) {
     double c64[3], xb64[3];
     part_chis(*k64, x, y, z, c64, xb64);
     return part_of_max(c64);
@@ -735,7 +733,7 @@ __device__ __attribute__((noinline)) int part_of_max64(const KinT<double>* k64, 
 //
 // defer != nullptr: where two parts overlap, set *defer and return an empty
 // point instead of deciding (the caller revisits such points with k64).
-template <typename TM>
+template <typename TM, bool WINGS = true>
 __device__ __forceinline__ MaskPt<TM> eval_mask(const KinT<TM>& k, double x, double y, double z,
                                                 const KinT<double>* k64, bool* defer = nullptr) {
     MaskPt<TM> o;
@@ -748,7 +746,8 @@ __device__ __forceinline__ MaskPt<TM> eval_mask(const KinT<TM>& k, double x, dou
         if (r0 * r0 + r1 * r1 + r2c * r2c > k.r2all) return o;
     }
     TM c[3], xb[3];
-    part_chis(k, xt, yt, zt, c, xb);
+    part_chis<WINGS>(k, xt, yt, zt, c, xb);
+    mask_stage();
     const TM chimax = fmax(c[0], fmax(c[1], c[2]));
     if (chimax <= TM(0)) return o;
     int part;

@@ -21,6 +21,7 @@
 #include "common.hpp"
 #include "fft.hpp"
 #include "insect.hpp"
+#include "xrow.hpp"
 
 namespace flusi {
 
@@ -575,7 +576,10 @@ __device__ __forceinline__ void block_reduce_store(const double (&acc)[NVAL], do
 
 // ---------------------------------------------------------------------------
 // x-pass: inverse x, pointwise source with the mask, FP64 partial sums,
-// forward x.  Reduction values per workgroup:
+// forward x, by the row kernel (xpass_rows), or for rows of 1024 points or more by
+// LDS tiles (xpass_tile; twiddles from the table in memory, as staging it for
+// every workgroup costs more there: 1152 points, FP32 one-row tiles 35.4 ms with
+// LDS twiddles, 18.6 ms without).  Reduction values per workgroup:
 //   [0] max |u|^2, [1] sum |u|^2 (non-finite values propagate into it), [2] 0,
 //   [3 + 12 c + 0..2]  sum chi (u - u_s)            (colour c+1)
 //   [3 + 12 c + 3..5]  sum (x - x_ref) x chi (u - u_s)
@@ -586,23 +590,6 @@ __device__ __forceinline__ void block_reduce_store(const double (&acc)[NVAL], do
 // Member table: N*N/RW workgroups per member, y-partials in bufB, output in bufA.
 // SP: members with the vorticity sponge; chi_sp * w is transformed beside N
 // and stored as fields 3..5.
-// Workgroups per CU the x-pass asks the compiler to fit (registers), where
-// its LDS allows: the FP32 full-size tile without the sponge (its twiddles are
-// then read from the table in memory, and the three-colour tile also drops the
-// column pad, keeping the tile under 40 KiB); not at nx = 512, where the
-// 128-register budget spills.
-template <typename T, int NX, int NC, int V, bool SP>
-__host__ __device__ constexpr int xpass_min_blocks() {
-    return (sizeof(T) < 8 && V == 0 && !SP && NX < 512) ? 4 : 1;
-}
-// Column stride of the x-pass tile: the FFT layout's (cm_stride), without its
-// one-element pad for the three-colour tile at 4 workgroups per CU (the pad
-// spreads the column starts over the LDS banks; without it 256^3 and 128^3
-// measured no slower, and the tile fits in 40 KiB).
-template <typename T, int NX, int NC, int V, bool SP>
-__host__ __device__ constexpr int xpass_stride() {
-    return (NC > 1 && xpass_min_blocks<T, NX, NC, V, SP>() == 4) ? NX + NX / 16 : cm_stride(NX);
-}
 // Threads per x-pass workgroup: NT, except for one-row tiles of rows of 1024
 // points or more, whose columns take 32 lanes each (36 values per lane at
 // 1152): there the row's 3 inverse and 2 forward column transforms would leave
@@ -613,9 +600,509 @@ __host__ __device__ constexpr int xpass_threads() {
     return (NX >= 1024 && rows_x(NX, sizeof(cx<T>), V) == 1 && (sizeof(T) < 8 || !SP)) ? 128 : NT;
 }
 
+// Rows of at most 512 points go through the register row kernel (xpass_rows).
+// A wavefront takes P sets of 64/G rows, one after the other; with P = 2 the N_z
+// of a row pair share one forward transform, with P = 1 each row transforms its
+// own (small grids, where the shorter chain per wavefront counts more than the
+// tenth of the transforms it adds, and the sponge, whose second kept field would
+// cost LDS).  xrow_R: wavefronts with rows per workgroup, 4 >> V (row pairs; as
+// many rows per workgroup also with P = 1, since every member of a launch has the
+// same workgroup count), fewer where the rows do not divide.  Small grids
+// (xrow_share) instead spread over the CUs, and the wavefronts of a workgroup,
+// four with a body, take the points near it together: there one wavefront's chain
+// of mask evaluations would be the length of the kernel.
+template <int NX>
+__host__ __device__ constexpr bool xrow_on() { return xr_E(NX) > 0; }
+__host__ __device__ constexpr bool xrow_share(int NX) { return NX <= 128; }
+__host__ __device__ constexpr int xrow_P(int NX, int cbytes, bool SP) {
+    return xrow_share(NX) || SP || (cbytes > 8 && xr_E(NX) <= 8) ? 1 : 2;
+}
+__host__ __device__ constexpr int xrow_set(int NX, int cbytes, bool SP) {
+    return 64 / (NX / xr_E(NX)) * xrow_P(NX, cbytes, SP);
+}
+// rows per workgroup
+__host__ __device__ constexpr int xrow_rows(int NX, int N, int cbytes, int V) {
+    const int set = xrow_set(NX, cbytes, false);
+    int w = cbytes > 8 && xr_E(NX) > 8 ? 2 : 4;
+    if (xrow_share(NX))
+        while (w > 1 && N * N / (w * set) < 256) w >>= 1;
+    w >>= V;
+    if (w < 1) w = 1;
+    while (N * N % (w * set) != 0) w >>= 1;
+    return w * set;
+}
+__host__ __device__ constexpr int xrow_R(int NX, int N, int cbytes, int V, bool SP) {
+    return xrow_rows(NX, N, cbytes, V) / xrow_set(NX, cbytes, SP);
+}
+__host__ __device__ constexpr int xrow_W(int NX, int N, int cbytes, int NC, int V, bool SP) {
+    const int R = xrow_R(NX, N, cbytes, V, SP);
+    return xrow_share(NX) && NC > 0 && R < 4 ? 4 : R;
+}
+// rows per workgroup of the x-pass
+template <typename T, int NX, int N>
+__host__ __device__ constexpr int xpass_wg_rows(int V) {
+    if constexpr (xrow_on<NX>()) return xrow_rows(NX, N, sizeof(cx<T>), V);
+    else return rows_x(NX, sizeof(cx<T>), V);
+}
 template <typename T, int NX, int N, int NC, int V, bool SP>
-__global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<T, NX, NC, V, SP>())) void k_xpass(
-    const Member* __restrict__ mt, const cx<T>* __restrict__ tw) {
+__host__ __device__ constexpr int xpass_block() {
+    if constexpr (xrow_on<NX>()) return 64 * xrow_W(NX, N, sizeof(cx<T>), NC, V, SP);
+    else return xpass_threads<T, NX, V, SP>();
+}
+template <typename T, int NX, int NC, int V, bool SP>
+__host__ __device__ constexpr int xpass_waves() {
+    if constexpr (xrow_on<NX>()) return sizeof(T) < 8 ? (xr_E(NX) > 8 ? 2 : (NC == 0 ? 4 : 3)) : (xr_E(NX) > 8 && !xrow_share(NX) ? 1 : 2);
+    else return 1;
+}
+
+// Conservative test of which points of a row can have chi > 0, so that the mask
+// itself is evaluated with such points in neighbouring lanes.  Rows 0..2 of aff:
+// the body frame's coordinates as affine functions of the global ones (three
+// coefficients and a constant) and the half-widths beyond which the thorax's
+// chi is 0; rows 3..5 and 6..8: the same of the wings' frames about their
+// outlines' centres (an ellipse's delta exceeds thr where |e_x| > A + thr, as
+// the overshoot beyond the outline along the ray from the centre is at least
+// its x component).  The half-widths carry a margin far above the rounding.
+template <typename T>
+__device__ __forceinline__ void mask_frames(const KinT<T>& k, T side, T* aff, int r) {
+    const int w = r / 3 - 1, i = r % 3;
+    T c[3], o = T(0), h;
+    if (r < 3) {
+        for (int q = 0; q < 3; ++q) c[q] = k.Mb[3 * i + q];
+        h = i == 0 ? k.ea : k.eb;
+    } else {
+        const T* M = k.Mws[w] + 3 * i;
+        for (int q = 0; q < 3; ++q) c[q] = M[0] * k.Mb[q] + M[1] * k.Mb[3 + q] + M[2] * k.Mb[6 + q];
+        o = -(M[0] * k.piv[w][0] + M[1] * k.piv[w][1] + M[2] * k.piv[w][2]);
+        const bool poly = k.wshape == FLUSI_WING_FOURIER;
+        if (i == 0) {
+            o -= k.wcx;
+            h = poly ? k.wrad : k.wA;
+        } else if (i == 1) {
+            o -= k.wcy;
+            h = poly ? k.wrad : k.wB;
+        } else {
+            h = T(0.5) * k.wt;
+        }
+    }
+    const T oc = c[0] * k.xc[0] + c[1] * k.xc[1] + c[2] * k.xc[2];
+    const T sc = side + fabs(k.xc[0]) + fabs(k.xc[1]) + fabs(k.xc[2]) + fabs(o);
+    for (int q = 0; q < 3; ++q) aff[5 * r + q] = c[q];
+    aff[5 * r + 3] = o - oc;
+    aff[5 * r + 4] = h + k.thr + T(1e-5) * sc;
+}
+// Bit t: element l + G t of the row at (y, z), at distance^2 r2 from the x axis
+// through the body's centre.
+template <typename T, int E, int G, int NC>
+__device__ __forceinline__ unsigned mask_candidates(const KinT<T>& k, const T* aff, T dx, T y, T z, T r2, int l) {
+    // keep the constants in LDS (not hoisted into registers)
+    __asm__ volatile("" ::: "memory");
+    unsigned cand = 0;
+    const T x0 = dx * T(l), dg = dx * T(G);
+    const T xc = k.xc[0], rb = k.r2b * T(1.0 + 1e-5);
+    if (k.body == FLUSI_BODY_ELLIPSOID && !k.nsph) {
+        const T y0 = aff[6] * y + aff[7] * z + aff[8], z0 = aff[11] * y + aff[12] * z + aff[13];
+        const T y1 = aff[5], z1 = aff[10], h = aff[9] > aff[14] ? aff[9] : aff[14];
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            const T x = x0 + dg * T(t), d = x - xc, a = y0 + y1 * x, b = z0 + z1 * x;
+            if ((r2 + d * d <= rb) & (a * a + b * b <= h * h)) cand |= 1u << t;
+        }
+    } else if (k.body != FLUSI_BODY_NONE) {
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+            const T d = x0 + dg * T(t) - xc;
+            if (r2 + d * d <= rb) cand |= 1u << t;
+        }
+    }
+    if constexpr (NC > 1) {
+        if (k.wings) {
+#pragma unroll 1
+            for (int w = 0; w < 2; ++w) {
+                const T* f = aff + 15 + 15 * w;
+                const T p0 = f[1] * y + f[2] * z + f[3], q0 = f[6] * y + f[7] * z + f[8], s0 = f[11] * y + f[12] * z + f[13];
+                const T p1 = f[0], q1 = f[5], s1 = f[10], ph = f[4], qh = f[9], sh = f[14];
+#pragma unroll
+                for (int t = 0; t < E; ++t) {
+                    const T x = x0 + dg * T(t);
+                    if ((fabs(p0 + p1 * x) <= ph) & (fabs(q0 + q1 * x) <= qh) & (fabs(s0 + s1 * x) <= sh)) cand |= 1u << t;
+                }
+            }
+        }
+    }
+    return cand;
+}
+
+// The x-pass of rows held in registers (xr_fft).  R wavefronts with rows, W in all
+// (those beyond R only evaluate the mask).
+// Bound: at large grids the vector units and the waves' latency (65536 rows of
+// 256 points: 690 VALU instructions per row against 1050 of LDS column tiles, and
+// no workgroup barrier between the stages), with the traffic not far below (411
+// MB at 256^3 FP32, 86 us at the rate of a large copy).  Measured per launch, LDS
+// column tiles -> this: 256^3 without a body FP32 168 -> 121 us, FP64 328 -> 224;
+// insect FP32 182 -> 147, FP64 343 -> 251; 512^3 insect FP32 1539 -> 1004; 192^3
+// insect FP64 202 -> 135; 128^3 insect FP32 34.9 -> 24.0, FP64 50.4 -> 36.0, with
+// the sponge FP64 98 -> 50; 64^3 insect FP32 23.1 -> 13.6.
+// The mask is evaluated on the points near the body only, gathered side by side
+// (mask_candidates): the parts cover a per mille of the box, and lanes without
+// them would go through the same instructions.
+template <typename T, int NX, int N, int NC, int R, int W, bool SP>
+__device__ __forceinline__ void xpass_rows(const Member& m, const cx<T>* __restrict__ tw, int wg) {
+    using G_ = Geo<T, NX, N>;
+    constexpr int K = G_::KX, KPp = G_::KPp;
+    constexpr int E = xr_E(NX), G = NX / E, NG = 64 / G, P = xrow_P(NX, sizeof(cx<T>), SP), SC = xr_stride(NX);
+    constexpr long fs = (long)N * N * KPp;
+    constexpr bool K64 = NC > 1 && sizeof(T) < 8;
+    constexpr int NVAL = 3 + 12 * NC;
+    constexpr bool SHARE = xrow_share(NX) && NC > 0;
+    static_assert(R == W || SHARE, "wavefronts without rows share lists");
+    constexpr int CAP = 64 * E;  // points of one sweep over the wavefront's rows
+    // LDS of a wavefront: the exchange buffers of its rows; between the inverse
+    // and the forward transforms the same bytes hold the list of the points near
+    // the body (velocity, then penalization term) and their ids
+    constexpr size_t XB = sizeof(cx<T>) * NG * SC;
+    constexpr size_t LB = NC > 0 ? 3 * sizeof(T) * CAP + sizeof(unsigned short) * CAP : 0;
+    constexpr size_t WB = ((XB > LB ? XB : LB) + 15) / 16 * 16;
+    __shared__ __align__(16) unsigned char lds[R * WB];
+    // N_z (and chi_sp w_z) of the first row of two, kept for the transform that
+    // the second shares with it
+    __shared__ T nzl[P == 2 ? R * CAP : 1], szl[P == 2 && SP ? R * CAP : 1];
+    __shared__ int counts[SHARE ? R : 1];  // points near the body of each wavefront's rows
+    __shared__ double wred[W][NVAL];
+    __shared__ KinT<T> kin;
+    __shared__ cx<T> tws[NX];
+    __shared__ typename std::conditional<K64, KinT<double>, char>::type kin64;
+    __shared__ T aff[NC > 0 ? 45 : 1];
+    const StateHdr* __restrict__ hdr = m.hdr;
+    if (*gview(&hdr->status)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    xr_twiddles<T, NX>(tws, tw, 64 * W);
+    const int l0 = lane % G, g = lane / G;
+    const bool rows = R == W || wv < R;
+    const int row0 = __builtin_amdgcn_readfirstlane((wg * R + (rows ? wv : 0)) * NG * P);
+    const glb<cx<T>>* __restrict__ yin = gview(static_cast<const cx<T>*>(m.bufB));
+    glb<cx<T>>* __restrict__ xout = gview(static_cast<cx<T>*>(m.bufA));
+    const double dx = m.dx;
+    unsigned char* mine = lds + (rows ? wv : 0) * WB;
+    cx<T>* col = reinterpret_cast<cx<T>*>(mine) + g * SC;
+    T* lu = reinterpret_cast<T*>(mine);
+    unsigned short* li = reinterpret_cast<unsigned short*>(mine + 3 * sizeof(T) * CAP);
+    if constexpr (NC > 0) {
+        // kinematics block prepared once per time level (state header) -> LDS
+        const glb<unsigned>* a;
+        if constexpr (sizeof(T) < 8) a = gview(reinterpret_cast<const unsigned*>(&hdr->kf));
+        else a = gview(reinterpret_cast<const unsigned*>(&hdr->kd));
+        unsigned* b = reinterpret_cast<unsigned*>(&kin);
+        for (int e = tid; e < (int)(sizeof(KinT<T>) / 4); e += 64 * W) b[e] = a[e];
+    }
+    if constexpr (K64) {
+        // FP64 kinematics for the part choice where parts overlap
+        const glb<double>* a = gview(reinterpret_cast<const double*>(&hdr->kd));
+        double* b = reinterpret_cast<double*>(&kin64);
+        for (int e = tid; e < (int)(sizeof(KinT<double>) / 8); e += 64 * W) b[e] = a[e];
+    }
+    if (lane < NVAL) wred[wv][lane] = 0.0;
+    __syncthreads();
+    if constexpr (NC > 0) {
+        if (tid < 9) mask_frames(kin, T(dx * (NX > N ? NX : N)), aff, tid);
+        __syncthreads();
+    }
+    const KinT<double>* k64p = nullptr;
+    if constexpr (K64) k64p = &kin64;
+    const T s = T(1.0 / ((double)NX * (double)N * (double)N));
+    const T ie = T(m.inv_eta);
+    double umax2 = 0.0, usum = 0.0;
+
+    // forward transform of v and the split into two real fields' modes 0..K,
+    // stored to oa and, with two set, to ob (the wavefront's first row there)
+    const auto forward = [&](cx<T> (&v)[E], glb<cx<T>>* oa, glb<cx<T>>* ob, bool two) {
+        xr_fft<T, NX, -1>(v, col, l0, tws);
+        const int l = xr_lane<G>(l0);
+        // the conjugate modes lie on other lanes
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if constexpr (xr_mode(NX, K, t) >= 3) col[l + G * t] = v[t];
+        });
+        wave_sync();
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            constexpr int md = xr_mode(NX, K, t);
+            if constexpr (md == 1 || md == 2) {
+                const int k = l + G * t;
+                if (md == 1 || k <= K) {
+                    const cx<T> zk = v[t];
+                    cx<T> zm = zk;
+                    if (t > 0 || l > 0) zm = col[NX - k];
+                    gst(oa, (unsigned)(g * KPp + k), cx<T>{T(0.5) * (zk.x + zm.x), T(0.5) * (zk.y - zm.y)});
+                    if (two) gst(ob, (unsigned)(g * KPp + k), cx<T>{T(0.5) * (zk.y + zm.y), T(-0.5) * (zk.x - zm.x)});
+                }
+            }
+        });
+        wave_sync();
+    };
+
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+        const int row = row0 + p * NG + g, l = xr_lane<G>(l0);
+        cx<T> z[3][E];
+        unsigned cand = 0;  // elements that can have chi > 0
+        int cnt = 0;        // ... of the wavefront's rows
+        if (rows) {
+        // 1. the three Hermitian pairs of the row, packed as Z = X + iY over the
+        //    full axis, and their inverse transforms
+        {
+            // two fields' loads ahead of the transform that waits for the first
+            cx<T> a[3][E], b[3][E];
+            const auto load = [&](auto pc) {
+                constexpr int c = decltype(pc)::value;
+                // uniform base and a 32-bit offset per lane
+                const glb<cx<T>>* A = yin + (2 * c) * fs + (long)(row0 + p * NG) * KPp;
+                const glb<cx<T>>* B = A + fs;
+                static_for<E>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    constexpr int md = xr_mode(NX, K, t);
+                    const int k = md >= 3 ? NX - l - G * t : l + G * t;
+                    a[c][t] = b[c][t] = cx<T>{T(0), T(0)};
+                    if constexpr (md != 0) {
+                        if (md == 1 || md == 3 || k <= K) {
+                            a[c][t] = gld(A, (unsigned)(g * KPp + k));
+                            b[c][t] = gld(B, (unsigned)(g * KPp + k));
+                        }
+                    }
+                });
+            };
+            load(std::integral_constant<int, 0>{});
+            load(std::integral_constant<int, 1>{});
+            static_for<3>([&](auto pc) {
+                constexpr int c = decltype(pc)::value;
+                static_for<E>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    constexpr int md = xr_mode(NX, K, t);
+                    const cx<T> x = a[c][t], y = b[c][t];
+                    if constexpr (md == 0) z[c][t] = cx<T>{T(0), T(0)};
+                    else if constexpr (md >= 3) z[c][t] = cx<T>{x.x + y.y, y.x - x.y};
+                    else z[c][t] = cx<T>{x.x - y.y, x.y + y.x};
+                    if constexpr (t == 0) {
+                        if (l == 0) z[c][t] = cx<T>{x.x, y.x};
+                    }
+                });
+                if constexpr (c == 0) load(std::integral_constant<int, 2>{});
+                xr_fft<T, NX, +1>(z[c], col, l0, tws);
+            });
+        }
+        const int j = row % N, kz = row / N;
+        const double yg = dx * j, zg = dx * kz;
+        if constexpr (NC > 0) {
+            // whether a point of the wavefront's rows can lie inside the body's
+            // cull sphere (radius^2 r2all about xc, beyond which chi == 0
+            // exactly): the rows span the whole x axis, so only their (y, z)
+            // distance counts; taken in FP64 with a margin far above the rounding
+            // of the per-point test
+            const double dy = yg - (double)kin.xc[1], dz = zg - (double)kin.xc[2];
+            const double r2 = dy * dy + dz * dz;
+            if (__any(r2 <= (double)kin.r2all * (1.0 + 1e-5))) {
+                cand = mask_candidates<T, E, G, NC>(kin, aff, T(dx), T(yg), T(zg), T(r2), l);
+                // their velocities side by side in LDS
+                if (__any(cand != 0)) {
+                    static_for<E>([&](auto tc) {
+                        constexpr int t = decltype(tc)::value;
+                        const bool q = (cand >> t) & 1u;
+                        const unsigned long long bal = __ballot(q);
+                        if (q) {
+                            const int pos = cnt + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                                            __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                            lu[pos] = z[0][t].x * s;
+                            lu[CAP + pos] = z[0][t].y * s;
+                            lu[2 * CAP + pos] = z[1][t].x * s;
+                            li[pos] = (unsigned short)(lane | t << 6);
+                        }
+                        cnt += __popcll(bal);
+                    });
+                }
+            }
+        }
+        // 2. pointwise source and partial sums
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            const T ux = z[0][t].x * s, uy = z[0][t].y * s, uz = z[1][t].x * s;
+            const T wx = z[1][t].y * s, wy = z[2][t].x * s, wz = z[2][t].y * s;
+            T nx = uy * wz - uz * wy;
+            T ny = uz * wx - ux * wz;
+            T nzt = ux * wy - uy * wx;
+            const double u2 = (double)ux * ux + (double)uy * uy + (double)uz * uz;
+            // a non-finite value reaches the FP64 sum (NaN and Inf propagate
+            // through additions), which the step checks
+            umax2 = fmax(umax2, u2);
+            usum += u2;
+            const double xg = dx * (l + G * t);
+            // Dirichlet layer (Sec. 2.3): penalized to u_wall, with no body terms
+            if (m.wall) {
+                if (xg >= m.wall_lo[0] || yg >= m.wall_lo[1] || zg >= m.wall_lo[2]) {
+                    nx -= ie * (ux - T(m.u_wall[0]));
+                    ny -= ie * (uy - T(m.u_wall[1]));
+                    nzt -= ie * (uz - T(m.u_wall[2]));
+                }
+            }
+            z[0][t] = cx<T>{nx, ny};
+            z[2][t].x = nzt;
+            if constexpr (SP) {
+                // vorticity sponge: chi_sp * w, transformed like N
+                const bool in = xg >= m.sp_lo[0] || yg >= m.sp_lo[1] || zg >= m.sp_lo[2];
+                const T c = in ? T(1) : T(0);
+                z[1][t] = cx<T>{c * wx, c * wy};
+                z[2][t].y = c * wz;
+            }
+        });
+        }
+        if constexpr (NC > 0) {
+            // the points near the body, in lanes side by side: mask, penalization
+            // term and FP64 force sums; of the wavefront's rows, or of all the
+            // workgroup's together
+            cnt = __builtin_amdgcn_readfirstlane(cnt);
+            int total = cnt;
+            if constexpr (SHARE) {
+                if (rows && lane == 0) counts[wv] = cnt;
+                __syncthreads();
+                total = 0;
+                for (int w = 0; w < R; ++w) total += counts[w];
+            }
+            if (total > 0) {
+                wave_sync();
+                constexpr int STEP = SHARE ? 64 * W : 64;
+                const int first = SHARE ? tid : lane;
+#pragma unroll 1
+                for (int i0 = 0; i0 < total; i0 += STEP) {
+                    // keep the kinematics block in LDS (not hoisted into registers)
+                    __asm__ volatile("" ::: "memory");
+                    int i = i0 + first, w = 0;
+                    const bool act = i < total;
+                    T* eu = lu;
+                    const unsigned short* ei = li;
+                    if constexpr (SHARE) {
+                        if (act)
+                            while (i >= counts[w]) i -= counts[w++];
+                        eu = reinterpret_cast<T*>(lds + w * WB);
+                        ei = reinterpret_cast<const unsigned short*>(lds + w * WB + 3 * sizeof(T) * CAP);
+                    }
+                    const int rw0 = SHARE ? (wg * R + w) * NG * P : row0;
+                    const int id = act ? (int)ei[i] : 0;
+                    const int ln = id & 63, xi = ln % G + G * (id >> 6), rr = rw0 + p * NG + ln / G;
+                    const double xg = dx * xi, yg = dx * (rr % N), zg = dx * (rr / N);
+                    MaskPt<T> mp;
+                    mp.chi = T(0);
+                    mp.us[0] = mp.us[1] = mp.us[2] = T(0);
+                    mp.colour = 0;
+                    const bool inwall = m.wall && (xg >= m.wall_lo[0] || yg >= m.wall_lo[1] || zg >= m.wall_lo[2]);
+                    if (act && !inwall) mp = eval_mask<T, (NC > 1)>(kin, xg, yg, zg, k64p);
+                    const bool has = mp.chi > T(0);
+                    T ux = T(0), uy = T(0), uz = T(0);
+                    if (act) {
+                        ux = eu[i];
+                        uy = eu[CAP + i];
+                        uz = eu[2 * CAP + i];
+                        const T pen = mp.chi * ie;
+                        eu[i] = pen * (ux - mp.us[0]);
+                        eu[CAP + i] = pen * (uy - mp.us[1]);
+                        eu[2 * CAP + i] = pen * (uz - mp.us[2]);
+                    }
+                    // every lane takes part in the wave sums (lanes of other colours
+                    // add 0); the twelve terms of a colour are formed only where it
+                    // is present
+                    const int ci = has ? mp.colour - 1 : -1;
+                    static_for<NC>([&](auto cc) {
+                        constexpr int colour = decltype(cc)::value;
+                        const bool own = ci == colour;
+                        if (__any(own)) {
+                            const double ch = mp.chi, s0 = mp.us[0], s1 = mp.us[1], s2 = mp.us[2];
+                            const double f[3] = {ch * ((double)ux - s0), ch * ((double)uy - s1), ch * ((double)uz - s2)};
+                            const double q[3] = {ch * s0, ch * s1, ch * s2};
+                            const double rx = xg - kin.xref[colour][0], ry = yg - kin.xref[colour][1],
+                                         rz = zg - kin.xref[colour][2];
+                            const double tt[12] = {f[0], f[1], f[2],
+                                                   ry * f[2] - rz * f[1], rz * f[0] - rx * f[2], rx * f[1] - ry * f[0],
+                                                   q[0], q[1], q[2],
+                                                   ry * q[2] - rz * q[1], rz * q[0] - rx * q[2], rx * q[1] - ry * q[0]};
+                            double v[12], sr[3];
+#pragma unroll
+                            for (int e = 0; e < 12; ++e) v[e] = own ? tt[e] : 0.0;
+                            wave_sum12(v, sr);
+                            if ((lane & 15) == 15) {
+#pragma unroll
+                                for (int e = 0; e < 3; ++e) wred[wv][3 + 12 * colour + 3 * (lane >> 4) + e] += sr[e];
+                            }
+                        }
+                    });
+                }
+                if constexpr (SHARE) __syncthreads();
+                else wave_sync();
+                int at = 0;
+                static_for<E>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    const bool q = (cand >> t) & 1u;
+                    const unsigned long long bal = __ballot(q);
+                    if (q) {
+                        const int pos = at + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                        z[0][t].x -= lu[pos];
+                        z[0][t].y -= lu[CAP + pos];
+                        z[2][t].x -= lu[2 * CAP + pos];
+                    }
+                    at += __popcll(bal);
+                });
+                wave_sync();
+            }
+        }
+        if (!rows) continue;
+        // 3. forward transforms of (N_x, N_y), and of chi_sp (w_x, w_y)
+        glb<cx<T>>* o = xout + (long)(row0 + p * NG) * KPp;
+        forward(z[0], o, o + fs, true);
+        if constexpr (SP) forward(z[1], o + 3 * fs, o + 4 * fs, true);
+        // ... and of the rows' N_z (chi_sp w_z)
+        T* keep = nzl + (P == 2 ? wv * CAP + lane : 0);
+        T* skeep = szl + (P == 2 && SP ? wv * CAP + lane : 0);
+        if (P == 2 && p == 0) {
+            static_for<E>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                keep[t * 64] = z[2][t].x;
+                if constexpr (SP) skeep[t * 64] = z[2][t].y;
+            });
+        } else {
+            o = xout + 2 * fs + (long)row0 * KPp;
+            cx<T> v[E];
+            static_for<E>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                v[t] = P == 2 ? cx<T>{keep[t * 64], z[2][t].x} : cx<T>{z[2][t].x, T(0)};
+            });
+            forward(v, o, o + NG * KPp, P == 2);
+            if constexpr (SP) {
+                static_for<E>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    v[t] = P == 2 ? cx<T>{skeep[t * 64], z[2][t].y} : cx<T>{z[2][t].y, T(0)};
+                });
+                forward(v, o + 3 * fs, o + 3 * fs + NG * KPp, P == 2);
+            }
+        }
+    }
+    // partial sums of the workgroup, combined over its wavefronts in a fixed order
+    umax2 = wave_max(umax2);
+    usum = wave_sum(usum);
+    if (lane == 0) {
+        wred[wv][0] = umax2;
+        wred[wv][1] = usum;
+    }
+    if constexpr (W > 1) __syncthreads();
+    else wave_sync();
+    if (tid < NV) {
+        double r = 0.0;
+        if (tid < NVAL)
+            for (int w = 0; w < W; ++w) r = w == 0 ? wred[0][tid] : (tid == 0 ? fmax(r, wred[w][tid]) : r + wred[w][tid]);
+        gview(m.partial)[(long)wg * NV + tid] = r;
+    }
+}
+
+// Rows of 1024 points or more: columns in LDS tiles.
+template <typename T, int NX, int N, int NC, int V, bool SP>
+__device__ __forceinline__ void xpass_tile(const Member* __restrict__ mt, const cx<T>* __restrict__ tw) {
     constexpr int NT = xpass_threads<T, NX, V, SP>();  // this kernel's workgroup size
     using G = Geo<T, NX, N>;
     constexpr int K = G::KX, KP = G::KP, KPp = G::KPp;  // the x axis' cut
@@ -629,7 +1116,7 @@ __global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<
     const double dx = m.dx, inv_eta = m.inv_eta;
     glb<double>* __restrict__ partial = gview(m.partial);
     const int wg = blockIdx.x % NWG;
-    constexpr int SC = xpass_stride<T, NX, NC, V, SP>();
+    constexpr int SC = cm_stride(NX);
     // forward columns: (N_x, N_y) of each row, N_z of row pairs (one row:
     // N_z alone, with a zero imaginary part)
     constexpr int CI = 3 * RW, CF = RW == 1 ? 2 : 3 * RW / 2;
@@ -661,21 +1148,9 @@ __global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<
     // kinematics of those few points are read from the state header
     __shared__ unsigned amb[K64 ? (RW * NX + 31) / 32 : 1];
     __shared__ int amb_any;
-    // twiddles from LDS unless the table would cost a workgroup per CU (FP64,
-    // full-size tile: the tile alone is just under half of the 160 KiB), and
-    // not for rows of 1024 points or more, where staging the table for every
-    // workgroup costs more than the LDS reads save (1152 points, FP32: one-row
-    // tile 35.4 ms with LDS twiddles, 18.6 ms without)
-    constexpr bool TWL = !(sizeof(T) == 8 && V == 0) && xpass_min_blocks<T, NX, NC, V, SP>() == 1 && NX < 1024;
-    __shared__ cx<T> tws[TWL ? NX : 1];
     if (*gview(&hdr->status)) return;
     const int tid = threadIdx.x;
     const int row0 = wg * RW;
-    const cx<T>* twx = tw;
-    if constexpr (TWL) {
-        stage_twiddles<T, NX>(tws, tw, NT);
-        twx = tws;
-    }
     // kinematics blocks prepared once per time level (state header) -> LDS
     const auto lds_copy = [&](const void* src, void* dst, int bytes) {
         const glb<unsigned>* a = gview(static_cast<const unsigned*>(src));
@@ -734,7 +1209,7 @@ __global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<
             }
         }
     }
-    fft_cols<T, NX, +1, CI, NT, SC>(buf, twx);
+    fft_cols<T, NX, +1, CI, NT, SC>(buf, tw);
     // Whether any point of this workgroup's rows can lie inside the body's
     // cull sphere (radius^2 r2all about xc, beyond which chi == 0 exactly).
     // The rows span the whole x axis, so only their (y, z) distance counts; it
@@ -963,7 +1438,7 @@ __global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<
             partial[(long)wg * NV + tid] = r;
         }
     }
-    fft_cols<T, NX, -1, CFT, NT, SC>(fbuf, twx);
+    fft_cols<T, NX, -1, CFT, NT, SC>(fbuf, tw);
 
     // 3. split the packed spectra and store kx = 0..K
 #pragma unroll
@@ -985,6 +1460,18 @@ __global__ __launch_bounds__((xpass_threads<T, NX, V, SP>()), (xpass_min_blocks<
             }
             gst(O, r * KPp + k, v);
         }
+    }
+}
+
+template <typename T, int NX, int N, int NC, int V, bool SP>
+__global__ __launch_bounds__((xpass_block<T, NX, N, NC, V, SP>()), (xpass_waves<T, NX, NC, V, SP>())) void k_xpass(
+    const Member* __restrict__ mt, const cx<T>* __restrict__ tw) {
+    if constexpr (xrow_on<NX>()) {
+        constexpr int NWG = N * N / xpass_wg_rows<T, NX, N>(V);
+        xpass_rows<T, NX, N, NC, xrow_R(NX, N, sizeof(cx<T>), V, SP), xrow_W(NX, N, sizeof(cx<T>), NC, V, SP), SP>(
+            mt[blockIdx.x / NWG], tw, blockIdx.x % NWG);
+    } else {
+        xpass_tile<T, NX, N, NC, V, SP>(mt, tw);
     }
 }
 
@@ -1872,9 +2359,17 @@ __global__ void k_mask(const Kin* __restrict__ kin, int nx, int n, double dx, T*
     __shared__ KinT<T> kt;
     constexpr bool K64 = sizeof(T) < 8;
     __shared__ typename std::conditional<K64, KinT<double>, char>::type k64s;
-    if (threadIdx.x == 0) kin_cast<T>(*kin, kt);
+    // the blocks' arrays on all lanes of a wavefront each, the rest on its first
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+    if (wv == 0) {
+        kin_cast_arrays<T>(*kin, kt, ln, 64);
+        if (ln == 0) kin_cast_rest<T>(*kin, kt);
+    }
     if constexpr (K64) {
-        if (threadIdx.x == 64) kin_cast<double>(*kin, k64s);
+        if (wv == 1) {
+            kin_cast_arrays<double>(*kin, k64s, ln, 64);
+            if (ln == 0) kin_cast_rest<double>(*kin, k64s);
+        }
     }
     __syncthreads();
     const long npts = (long)nx * n * n;
