@@ -275,7 +275,7 @@ struct Impl final : ImplBase {
     using G = Geo<T, NX, N>;
     static constexpr int K = G::K, KP = G::KP, M = G::M, Q = G::Q;
     static constexpr int KPp = G::KPp, Qp = G::Qp;
-    static constexpr int C = cols_of(N), RW = rows_x(NX, sizeof(cx<T>)), NKX = NX / 2 + 1;
+    static constexpr int C = cols_of(N, sizeof(cx<T>)), RW = rows_x(NX, sizeof(cx<T>)), NKX = NX / 2 + 1;
     static constexpr int CZ = cols_z(N);
     static constexpr long N2 = (long)N * N, N3 = (long)NX * N * N;  // rows along x, points
     static constexpr long FULL = N2 * NKX;  // full-layout spectrum per field
@@ -316,7 +316,7 @@ struct Impl final : ImplBase {
     void colfft(PlanData& p, const CX* in, CX* out, int cols, int KX, long blk_in, long s_in, long blk_out,
                 long s_out, long fs_in, long fs_out, int nf) {
         const int nbx = (cols + C - 1) / C;
-        k_colfft<T, N, DIR, PIN, POUT><<<(unsigned)(nbx * nf), NT, 0, p.stream>>>(
+        k_colfft<T, N, DIR, PIN, POUT><<<(unsigned)(nbx * nf), nt_cols(N, sizeof(CX)), 0, p.stream>>>(
             in, out, cols, KX, blk_in, s_in, blk_out, s_out, fs_in, fs_out, tw(p), nbx);
     }
     void y_full(PlanData& p, const CX* in, CX* out, int nf, int dir) {
@@ -427,7 +427,7 @@ struct Impl final : ImplBase {
 
     // --- pruned stepping schedule over a member table ------------------------------
     template <int V>
-    static constexpr int nby(int nf) { return (N * KP + cols_of(N, V) - 1) / cols_of(N, V) * nf; }
+    static constexpr int nby(int nf) { return (N * KP + cols_of(N, sizeof(CX), V) - 1) / cols_of(N, sizeof(CX), V) * nf; }
     template <int V>
     static constexpr int nwg(int) { return (int)(N2 / xpass_wg_rows<T, NX, N>(V)); }
     static constexpr int NBZ = (Q + CZ - 1) / CZ;  // z-pass tiles per member
@@ -441,9 +441,9 @@ struct Impl final : ImplBase {
         const CX* w = static_cast<const CX*>(g.tw);
         constexpr int nb = nby<V>(6);
         if (kin_par >= 0)
-            k_ypass<T, NX, N, +1, 2, V><<<(unsigned)((nb + 1) * g.nmem), NT, 0, g.stream>>>(g.mt, nb, w, 6, kin_par);
+            k_ypass<T, NX, N, +1, 2, V><<<(unsigned)((nb + 1) * g.nmem), nt_cols(N, sizeof(CX), V), 0, g.stream>>>(g.mt, nb, w, 6, kin_par);
         else
-            k_ypass<T, NX, N, +1, 0, V><<<(unsigned)(nb * g.nmem), NT, 0, g.stream>>>(g.mt, nb, w, 6, 0);
+            k_ypass<T, NX, N, +1, 0, V><<<(unsigned)(nb * g.nmem), nt_cols(N, sizeof(CX), V), 0, g.stream>>>(g.mt, nb, w, 6, 0);
     }
     static void y_inverse(const GroupRun& g, int kin_par = -1) {
         if (g.sched.y_inverse == 2) y_inverse_v<2>(g, kin_par);
@@ -458,10 +458,10 @@ struct Impl final : ImplBase {
         const int nfwd = (g.n_nc[1][0] + g.n_nc[1][1] + g.n_nc[1][2]) ? 6 : 3;
         const int nb = nby<V>(nfwd);
         if (red)
-            k_ypass<T, NX, N, -1, 1, V><<<(unsigned)((nb + nred_of(NX, N)) * g.nmem), NT, 0, g.stream>>>(
+            k_ypass<T, NX, N, -1, 1, V><<<(unsigned)((nb + nred_of(NX, N)) * g.nmem), nt_cols(N, sizeof(CX), V), 0, g.stream>>>(
                 g.mt, nb + nred_of(NX, N), w, nfwd, nwg_of(g.sched.x_pass));
         else
-            k_ypass<T, NX, N, -1, 0, V><<<(unsigned)(nb * g.nmem), NT, 0, g.stream>>>(g.mt, nb, w, nfwd, 0);
+            k_ypass<T, NX, N, -1, 0, V><<<(unsigned)(nb * g.nmem), nt_cols(N, sizeof(CX), V), 0, g.stream>>>(g.mt, nb, w, nfwd, 0);
     }
     static void y_forward(const GroupRun& g, bool red) {
         if (g.sched.y_forward == 2) y_forward_v<2>(g, red);

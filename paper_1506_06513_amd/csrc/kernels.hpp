@@ -25,7 +25,7 @@
 
 namespace flusi {
 
-constexpr int NT = 256;   // threads per workgroup of the y passes and the x-pass
+constexpr int NT = 256;   // threads per workgroup of the x transforms and LDS tiles
 constexpr int NV = 39;    // reduction values per workgroup (see xpass)
 constexpr int NRED_MAX = 64;  // most first-level reduction workgroups per member
 
@@ -33,13 +33,25 @@ constexpr int NRED_MAX = 64;  // most first-level reduction workgroups per membe
 // values (V = 0 the default); a schedule picks one per pass (see the
 // autotuner).
 constexpr int NVARIANT = 3;
-// Columns per workgroup of the y passes: C*N ~ 4096 elements in LDS (V = 0),
-// a half (V = 1) or a quarter (V = 2) of that.
-__host__ __device__ constexpr int cols_of(int N, int V = 0) {
-    int c = 4096 / N, p = 8;
-    while (p * 2 <= c) p *= 2;
-    return p >> V;
+// Columns per workgroup of the column passes (y, and z of the full layout): 16
+// (V = 0), which is 128 bytes of every row in FP32; in FP64 half of that (still 128
+// bytes) where the LDS would leave a CU fewer than eight wavefronts (FP64
+// y-inverse with 8 / 16 columns: 256^3 231 / 212 us, 512^3 1823 / 1624, but 384^3
+// 535 / 686).  Twice as many (V = 1) within 512 threads and the LDS, or half (V = 2).
+// At least two wavefronts: the kinematics beside the y-inverse convert their two
+// blocks on one each.
+__host__ __device__ constexpr int cols_of(int N, int cbytes, int V = 0) {
+    const int G = N / xr_E(N, 1);
+    const int lds = xr_padded(N, 1) * cbytes;  // per column
+    int c = 16;
+    if (160 * 1024 / (c * lds) * c * G < 512 && c * G >= 256) c = 8;
+    if (V == 1 && 2 * c * G <= 512 && 2 * c * lds <= 120 * 1024) c *= 2;
+    if (V == 2) c /= 2;
+    while (c * G < 128) c *= 2;
+    return c;
 }
+// ... and its threads: one column element set per thread
+__host__ __device__ constexpr int nt_cols(int N, int cbytes, int V = 0) { return cols_of(N, cbytes, V) * (N / xr_E(N, 1)); }
 // Columns and threads per workgroup of the z-pass (more, narrower workgroups:
 // the z-pass has only (2K+1)(K+1) columns).  V = 1 and 2 use more threads per
 // column (fewer rows per thread): the smallest multiple of the V = 0 count
@@ -187,7 +199,7 @@ struct Member {
     double u_wall[3];           // ... with the velocity u_wall imposed
 };
 
-template <int NRED>
+template <int NRED, int NTH>
 __device__ inline void reduce_level1(const double* __restrict__ partial, int nwg, double* __restrict__ partial2,
                                      int b, double (*red)[NV]);
 
@@ -196,63 +208,85 @@ __device__ inline void reduce_level1(const double* __restrict__ partial, int nwg
 // Column q (q < Q) of a field starts at (q / KX) * blk + q % KX; element e of
 // the column sits at stride s.  PIN: the input holds only the 2K+1 kept
 // signed modes (pruned storage); POUT: only those are written.
+// Thread (c, l) holds the elements of column c congruent to l: it loads them and
+// stores its results itself, in rows of C columns, and LDS only carries the
+// exchanges between the butterfly stages (buf: xr_padded(N) * C values; tws: the
+// plan's twiddles, staged before the first exchange's barrier).
+// Bound: HBM at large grids (256^3 FP32 y-inverse 104 us, 4.3 TB/s; a large copy
+// runs at 4.8).  Measured per launch, columns staged in and out of LDS around the
+// transforms -> this: y-inverse FP32 512^3 969 -> 841 us, 384^3 409 -> 324, 192^3
+// 39 -> 31; y-forward FP32 512^3 489 -> 377, 128^3 10.5 -> 8.6; 32^3 FP64 both ways
+// 5.9 -> 3.4.
 // ---------------------------------------------------------------------------
+// element i of the thread's column, at a uniform base and a 32-bit byte offset
+template <typename T>
+__device__ __forceinline__ cx<T> gld_at(const glb<cx<T>>* base, unsigned byte) {
+    const auto* p = reinterpret_cast<const glb<cx<T>>*>(reinterpret_cast<const glb<char>*>(base) + byte);
+    return cx<T>{p->x, p->y};
+}
+template <typename T>
+__device__ __forceinline__ void gst_at(glb<cx<T>>* base, unsigned byte, cx<T> v) {
+    auto* p = reinterpret_cast<glb<cx<T>>*>(reinterpret_cast<glb<char>*>(base) + byte);
+    p->x = v.x;
+    p->y = v.y;
+}
 template <typename T, int N, int DIR, bool PIN, bool POUT, int C>
 __device__ __forceinline__ void colfft_tile(const glb<cx<T>>* __restrict__ in, glb<cx<T>>* __restrict__ out, int Q, int KX,
                                             long blk_in, long s_in, long blk_out, long s_out, int tile,
-                                            const cx<T>* __restrict__ tw, cx<T>* buf) {
-    constexpr int K = kmax_of(N);
-    constexpr int SC = cm_stride(N);
-    constexpr int RS = NT / C;      // rows handled per sweep
-    constexpr int RPT = N / RS;     // rows per thread
-    static_assert(NT % C == 0 && N % RS == 0, "column mapping");
-    const int tid = threadIdx.x;
-    const int c = tid % C, r0 = tid / C;
-    const int q = tile * C + c;
+                                            const cx<T>* tws, cx<T>* buf) {
+    constexpr int K = kmax_of(N), E = xr_E(N, 1), G = N / E;
+    const int c = threadIdx.x % C, l = threadIdx.x / C;
+    const int q0 = tile * C, b0 = q0 / KX;  // uniform: the tile's first block
+    const int q = q0 + c;
     const bool ok = q < Q;
-    const long bin = ok ? (long)(q / KX) * blk_in + q % KX : 0;
-    const long bout = ok ? (long)(q / KX) * blk_out + q % KX : 0;
-    cx<T> v[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        const int n = r0 + i * RS;
-        v[i] = cx<T>{T(0), T(0)};
-        if (ok) {
-            if constexpr (PIN) {
-                const int m = m_of_bin(n, N, K);
-                if (m >= 0) v[i] = gld(in, bin + m * s_in);
-            } else {
-                v[i] = gld(in, bin + n * s_in);
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) buf[c * SC + cpad(r0 + i * RS)] = v[i];
-    fft_cols<T, N, DIR, C, NT, SC>(buf, tw);
+    // offsets from the first block: within a few blocks and G elements of it
+    const int b = ok ? q / KX - b0 : 0, k = ok ? q - (b0 + b) * KX : 0;
+    in += b0 * blk_in;
+    out += b0 * blk_out;
+    const unsigned oi = (unsigned)((b * blk_in + k + l * s_in) * sizeof(cx<T>));
+    const unsigned oo = (unsigned)((b * blk_out + k + l * s_out) * sizeof(cx<T>));
+    cx<T> v[E];
     if (ok) {
-        constexpr int NOUT = POUT ? 2 * K + 1 : N;
-#pragma unroll
-        for (int i = 0; i < (NOUT + RS - 1) / RS; ++i) {
-            const int o = r0 + i * RS;
-            if (o < NOUT) {
-                const int n = POUT ? bin_of_m(o, N, K) : o;
-                gst(out, bout + o * s_out, buf[c * SC + cpad(n)]);
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            constexpr int md = PIN ? xr_mode(N, K, t, 1) : 1;
+            // storage row of element l + G t: itself, or past the dropped band
+            constexpr int r = md >= 3 ? G * t - N + 2 * K + 1 : G * t;
+            v[t] = cx<T>{T(0), T(0)};
+            if constexpr (md != 0) {
+                if (md == 1 || md == 3 || (md == 2 ? l + G * t <= K : l + G * t >= N - K)) v[t] = gld_at(in + r * s_in, oi);
             }
-        }
+        });
+    } else {
+        static_for<E>([&](auto tc) { v[decltype(tc)::value] = cx<T>{T(0), T(0)}; });
+    }
+    xr_fft<T, N, DIR, 1, C, true>(v, buf + c, l, tws);
+    if (ok) {
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            constexpr int md = POUT ? xr_mode(N, K, t, 1) : 1;
+            constexpr int r = md >= 3 ? G * t - N + 2 * K + 1 : G * t;
+            if constexpr (md != 0) {
+                if (md == 1 || md == 3 || (md == 2 ? l + G * t <= K : l + G * t >= N - K)) gst_at(out + r * s_out, oo, v[t]);
+            }
+        });
     }
 }
 
 // Column transforms of nf fields given by pointers (full-layout utilities):
 // 1D grid of nbx * nf workgroups.
 template <typename T, int N, int DIR, bool PIN, bool POUT>
-__global__ __launch_bounds__(NT) void k_colfft(const cx<T>* in, cx<T>* out, int Q, int KX, long blk_in, long s_in,
+__global__ __launch_bounds__((nt_cols(N, sizeof(cx<T>)))) void k_colfft(const cx<T>* in, cx<T>* out, int Q, int KX, long blk_in, long s_in,
                                                long blk_out, long s_out, long fs_in, long fs_out,
                                                const cx<T>* __restrict__ tw, int nbx) {
-    __shared__ cx<T> buf[cols_of(N) * cm_stride(N)];
+    constexpr int C = cols_of(N, sizeof(cx<T>));
+    __shared__ cx<T> buf[C * xr_padded(N, 1)];
+    __shared__ cx<T> tws[N];
+    xr_twiddles<T, N, 1>(tws, tw, nt_cols(N, sizeof(cx<T>)));
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int f = tile / nbx;
-    colfft_tile<T, N, DIR, PIN, POUT, cols_of(N)>(gview(in) + f * fs_in, gview(out) + f * fs_out, Q, KX, blk_in, s_in, blk_out, s_out,
-                                      tile % nbx, tw, buf);
+    colfft_tile<T, N, DIR, PIN, POUT, C>(gview(in) + f * fs_in, gview(out) + f * fs_out, Q, KX, blk_in, s_in, blk_out, s_out,
+                                      tile % nbx, tws, buf);
 }
 
 // Kinematics of member m and the mask-evaluation blocks its passes read, by one
@@ -431,13 +465,13 @@ __device__ __forceinline__ void kin_update(const Member& m, int p, bool at, doub
 // nfwd: forward fields per member (3, or 6 when a member of the launch has the
 // vorticity sponge; members without it skip fields 3..5).
 template <typename T, int NX, int N, int DIR, int EXTRA, int V>
-__global__ __launch_bounds__(NT, EXTRA == 2 ? 4 : 1) void k_ypass(const Member* __restrict__ mt, int per,
-                                                                  const cx<T>* __restrict__ tw, int nfwd, int nwg) {
+__global__ __launch_bounds__((nt_cols(N, sizeof(cx<T>), V)), EXTRA == 2 ? 4 : 1) void k_ypass(
+    const Member* __restrict__ mt, int per, const cx<T>* __restrict__ tw, int nfwd, int nwg) {
     using G = Geo<T, NX, N>;
     constexpr int KP = G::KP, KPp = G::KPp, Qp = G::Qp;
-    constexpr int C = cols_of(N, V);
+    constexpr int C = cols_of(N, sizeof(cx<T>), V), NTY = nt_cols(N, sizeof(cx<T>), V);
     constexpr int nbx = (N * KP + C - 1) / C;
-    constexpr size_t BUF = sizeof(cx<T>) * C * cm_stride(N);
+    constexpr size_t BUF = sizeof(cx<T>) * C * xr_padded(N, 1);
     constexpr size_t LDS = EXTRA == 2 && sizeof(KinShared) > BUF ? sizeof(KinShared) : BUF;
     const int nf = DIR > 0 ? 6 : nfwd;
     __shared__ __align__(16) unsigned char lds[LDS];
@@ -461,15 +495,15 @@ __global__ __launch_bounds__(NT, EXTRA == 2 ? 4 : 1) void k_ypass(const Member* 
     const int f = tile / nbx;
     if (f >= nf) {
         if constexpr (EXTRA == 1) {
-            __shared__ double red[NT / 64][NV];
+            __shared__ double red[NTY / 64][NV];
             if (tile - nf * nbx < nred_of(NX, N))
-                reduce_level1<nred_of(NX, N)>(m.partial, nwg, m.partial2, tile - nf * nbx, red);
+                reduce_level1<nred_of(NX, N), NTY>(m.partial, nwg, m.partial2, tile - nf * nbx, red);
         }
         return;
     }
     if (DIR < 0 && f >= 3 && !m.sponge) return;
     __shared__ cx<T> tws[N];
-    stage_twiddles<T, N>(tws, tw, NT);
+    xr_twiddles<T, N, 1>(tws, tw, NTY);
     const glb<cx<T>>* A = gview(static_cast<const cx<T>*>(m.bufA));
     glb<cx<T>>* B = gview(static_cast<cx<T>*>(m.bufB));
     if constexpr (DIR > 0)
@@ -605,9 +639,11 @@ __host__ __device__ constexpr int xpass_threads() {
 // of a row pair share one forward transform, with P = 1 each row transforms its
 // own (small grids, where the shorter chain per wavefront counts more than the
 // tenth of the transforms it adds, and the sponge, whose second kept field would
-// cost LDS).  xrow_R: wavefronts with rows per workgroup, 4 >> V (row pairs; as
-// many rows per workgroup also with P = 1, since every member of a launch has the
-// same workgroup count), fewer where the rows do not divide.  Small grids
+// cost LDS).  xrow_R: wavefronts with rows per workgroup, 2 (V = 0), 4 or 1 (as many
+// rows per workgroup also for the sponge's P = 1, since every member of a launch
+// has the same workgroup count), fewer where the rows do not divide; two have
+// less to wait for at the end than four (insect, 4 / 2 / 1: 256^3 FP32 152 / 140 /
+// 136 us, FP64 249 / 227 / 234; 512^3 FP32 988 / 932 / 1036).  Small grids
 // (xrow_share) instead spread over the CUs, and the wavefronts of a workgroup,
 // four with a body, take the points near it together: there one wavefront's chain
 // of mask evaluations would be the length of the kernel.
@@ -623,11 +659,13 @@ __host__ __device__ constexpr int xrow_set(int NX, int cbytes, bool SP) {
 // rows per workgroup
 __host__ __device__ constexpr int xrow_rows(int NX, int N, int cbytes, int V) {
     const int set = xrow_set(NX, cbytes, false);
-    int w = cbytes > 8 && xr_E(NX) > 8 ? 2 : 4;
-    if (xrow_share(NX))
+    int w = V == 0 || (V == 1 && cbytes > 8 && xr_E(NX) > 8) ? 2 : (V == 1 ? 4 : 1);
+    if (xrow_share(NX)) {
+        w = cbytes > 8 && xr_E(NX) > 8 ? 2 : 4;
         while (w > 1 && N * N / (w * set) < 256) w >>= 1;
-    w >>= V;
-    if (w < 1) w = 1;
+        w >>= V;
+        if (w < 1) w = 1;
+    }
     while (N * N % (w * set) != 0) w >>= 1;
     return w * set;
 }
@@ -1665,13 +1703,13 @@ __device__ inline void write_step(StateHdr* h, int p, const double* tot, const C
 
 // First level: workgroup b (< NRED) reduces the x-pass records
 // [b*chunk, (b+1)*chunk) ([workgroup][NV]).  Each wave reads whole records
-// (one coalesced load of NV doubles) and lane v accumulates value v; the four
-// waves take every fourth record and are combined in a fixed order.
-template <int NRED>
+// (one coalesced load of NV doubles) and lane v accumulates value v; the waves of
+// its NTH threads take turns at the records and are combined in a fixed order.
+template <int NRED, int NTH>
 __device__ inline void reduce_level1(const double* __restrict__ partial, int nwg, double* __restrict__ partial2,
                                      int b, double (*red)[NV]) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int NW = NT / 64;
+    constexpr int NW = NTH / 64;
     const int chunk = (nwg + NRED - 1) / NRED;
     const int lo = b * chunk, hi = min(nwg, lo + chunk);
     const bool is_max = lane == 0 || lane == 2;
