@@ -621,7 +621,7 @@ int flusi_autotune(flusi_plan plan, const void* state, const flusi_insect* ins, 
     sp.history = nullptr;
     const Member m = make_member(d, tmp, ins, sp);
     if (e == hipSuccess) {
-        k_member_set<<<1, 64, 0, d.stream>>>(d.member_dev, m, m.nc > 0 ? *ins : flusi_insect{});
+        k_member_set<<<1, NT_KIN, 0, d.stream>>>(d.member_dev, m, m.nc > 0 ? *ins : flusi_insect{});
         e = hipGetLastError();
     }
     int rc = FLUSI_OK;

@@ -111,6 +111,7 @@ struct GroupRun {
     bool any_dyn = false;
     bool any_ff = false;      // some member is in free flight
     bool rk = false;          // RK4 integrator (single-plan runs)
+    bool started = false;     // the prologue ran (with the launch record)
     // side stream for the kinematics kernel of the RK4 stages (null: they run
     // on `stream`): forked after the z-pass, joined before the x-pass, so they
     // overlap the y-inverse, which does not read them (the AB2 steps evaluate
@@ -552,9 +553,9 @@ struct Impl final : ImplBase {
     // level; the others use that dt, the kinematics of their own time and no
     // reduction.  The z-pass is always the fused form here.
     int run_steps_rk(const GroupRun& g, int nsteps) {
-        {
+        if (!g.started) {
             PassScope ps(g.prof, PASS_KIN, g.stream);
-            k_prologue<T><<<(unsigned)g.nmem, NT_KIN, 0, g.stream>>>(g.mt, g.nmem);
+            k_prologue<T><<<(unsigned)g.nmem, NT_KIN, 0, g.stream>>>(const_cast<Member*>(g.mt), 0, Member{}, flusi_insect{});
         }
         {
             PassScope ps(g.prof, PASS_ZINV, g.stream);
@@ -595,9 +596,9 @@ struct Impl final : ImplBase {
     int run_steps(const GroupRun& g, int nsteps) override {
         if (g.nmem <= 0 || nsteps <= 0) return FLUSI_OK;
         if (g.rk) return run_steps_rk(g, nsteps);
-        {
+        if (!g.started) {
             PassScope ps(g.prof, PASS_KIN, g.stream);
-            k_prologue<T><<<(unsigned)g.nmem, NT_KIN, 0, g.stream>>>(g.mt, g.nmem);
+            k_prologue<T><<<(unsigned)g.nmem, NT_KIN, 0, g.stream>>>(const_cast<Member*>(g.mt), 0, Member{}, flusi_insect{});
         }
         {
             PassScope ps(g.prof, PASS_ZINV, g.stream);
@@ -643,7 +644,7 @@ struct Impl final : ImplBase {
         flusi_step_params sp{};
         sp.mean_mode = FLUSI_MEAN_FREE;
         const Member m = make_member(p, st, nullptr, sp);
-        k_member_set<<<1, 64, 0, p.stream>>>(p.member_dev, m, flusi_insect{});
+        k_member_set<<<1, NT_KIN, 0, p.stream>>>(p.member_dev, m, flusi_insect{});
         k_hdr_init<<<1, 64, 0, p.stream>>>(static_cast<StateHdr*>(st), t0);
         x_r2c(p, static_cast<const T*>(u0), static_cast<CX*>(p.bufA), 3 * N2, KP, KPp);
         GroupRun g;
@@ -674,10 +675,14 @@ struct Impl final : ImplBase {
 
     int step(PlanData& p, void* st, const flusi_insect* ins, const flusi_step_params& sp) override {
         const Member m = make_member(p, st, ins, sp);
-        k_member_set<<<1, 64, 0, p.stream>>>(p.member_dev, m, m.nc > 0 ? *ins : flusi_insect{});
         if (m.nc > 0)
             if (int rc = prepare_wing_table(p, ins, p.stream)) return rc;
+        {
+            PassScope ps(&p, PASS_KIN, p.stream);
+            k_prologue<T><<<1, NT_KIN, 0, p.stream>>>(p.member_dev, 1, m, m.nc > 0 ? *ins : flusi_insect{});
+        }
         GroupRun g;
+        g.started = true;
         g.mt = p.member_dev;
         g.nmem = 1;
         g.n_nc[m.sponge][colour_slot(m.nc)] = 1;

@@ -289,8 +289,15 @@ __global__ __launch_bounds__((nt_cols(N, sizeof(cx<T>)))) void k_colfft(const cx
                                       tile % nbx, tws, buf);
 }
 
+// nbytes (a multiple of 8; both ends 8-byte aligned) copied by the workgroup.
+__device__ __forceinline__ void wg_copy8(void* dst, const void* src, int nbytes) {
+    auto* d = static_cast<unsigned long long*>(dst);
+    const auto* q = static_cast<const unsigned long long*>(src);
+    for (int i = threadIdx.x; i < nbytes / 8; i += blockDim.x) d[i] = q[i];
+}
+
 // Kinematics of member m and the mask-evaluation blocks its passes read, by one
-// workgroup (one wave or more).  The threads stage the body description in
+// workgroup (two waves or more).  The threads stage the body description in
 // LDS (one round trip instead of a chain of dependent loads) and evaluate the
 // sines and cosines in parallel, in two rounds: the angle series and fixed
 // angles, then the wing angles that the series give.  From those values one
@@ -322,13 +329,6 @@ static_assert(sizeof(flusi_insect) % 8 == 0 && sizeof(Kin) % 8 == 0 && sizeof(Ki
                   sizeof(KinT<double>) % 8 == 0 && offsetof(StateHdr, kin) % 8 == 0 &&
                   offsetof(StateHdr, kf) % 8 == 0 && offsetof(StateHdr, kd) % 8 == 0,
               "kinematics blocks are copied in 8-byte words");
-
-// nbytes (a multiple of 8; both ends 8-byte aligned) copied by the workgroup.
-__device__ __forceinline__ void wg_copy8(void* dst, const void* src, int nbytes) {
-    auto* d = static_cast<unsigned long long*>(dst);
-    const auto* q = static_cast<const unsigned long long*>(src);
-    for (int i = threadIdx.x; i < nbytes / 8; i += blockDim.x) d[i] = q[i];
-}
 
 template <typename T>
 __device__ __forceinline__ void kin_update(const Member& m, int p, bool at, double t_at, KinShared& s) {
@@ -371,21 +371,22 @@ __device__ __forceinline__ void kin_update(const Member& m, int p, bool at, doub
     for (int j = tid; j < n; j += nth)
         if (!s.dep[j]) s.val[j] = sin_cos(s.arg[j]);
     __syncthreads();
-    if (in.wings) {
-        if (tid == 0) {
-            double ang[3], rate[3];
-            wing_angle_values(in, s.t, ang, rate, TrigTable{s.arg, s.val, n, s.st != 0 ? 0 : 6});
-            kin_trig_args(in, s.t, s.st != 0, 1, ang, s.arg, s.dep);
-        }
-        __syncthreads();
-        for (int j = tid; j < n; j += nth)
-            if (s.dep[j]) s.val[j] = sin_cos(s.arg[j]);
-        __syncthreads();
-    }
-    // assembled in LDS: the block never occupies registers
+    // assembled in LDS: the block never occupies registers.  The body part needs
+    // none of the wing angles: it runs on the second wavefront while the first
+    // forms these and their sines
     Kin& k = s.k;
     const int st = s.st;
-    if (tid == 0) {
+    if (in.wings && tid < 64) {
+        if (tid == 0) {
+            double ang[3], rate[3];
+            wing_angle_values(in, s.t, ang, rate, TrigTable{s.arg, s.val, n, st != 0 ? 0 : 6});
+            kin_trig_args(in, s.t, st != 0, 1, ang, s.arg, s.dep);
+        }
+        wave_sync();
+        for (int j = tid; j < n; j += 64)
+            if (s.dep[j]) s.val[j] = sin_cos(s.arg[j]);
+    }
+    if (tid == 64) {
         const double rb = kin_body(in, s.t, m.dx, k, st != 0 ? s.y : nullptr, TrigTable{s.arg, s.val, n, 0});
         s.rall[0] = rb;
         if (!in.wings) {
@@ -434,7 +435,7 @@ __device__ __forceinline__ void kin_update(const Member& m, int p, bool at, doub
     // FP64 on the first wave and FP32 on the second where there is one
     constexpr bool F64 = sizeof(T) == 8;
     const bool need_kd = F64 || m.nc > 1, need_kf = !F64;
-    const int wv = tid >> 6, ln = tid & 63, wkf = nth > 64 ? 1 : 0;
+    const int wv = tid >> 6, ln = tid & 63, wkf = 1;
     if (need_kd && wv == 0) {
         kin_cast_arrays<double>(k, s.kd, ln, 64);
         if (ln == 0) kin_cast_rest<double>(k, s.kd);
@@ -1565,31 +1566,34 @@ __device__ inline Coef step_coef(const double* tot, const Slot& sl, StepCtl ctl,
     return c;
 }
 
-// Diagnostics of time level p and the next time level (one thread).  With a
+// What the writer workgroup stages in LDS: the current slot, the next one as it
+// is formed, and the kinematics of the level.
+struct StepShared {
+    Slot sl, nx;
+    Kin k;
+};
+static_assert(sizeof(Slot) % 8 == 0, "slots are copied in 8-byte words");
+
+// Diagnostics of time level p and the next time level, by one workgroup of 64
+// threads or more from values in LDS (tot: the totals; w.sl and w.k loaded).  With a
 // mask: the body's state at t^n (Sec. 3.6) and the wings' aerodynamic power (Sec. 3.5),
 // the moment of the solid momentum about the body centre for the next step's
 // unsteady torque term, and in free flight the total force and torque about
 // x_cntr that advance the body (the advance itself runs with the next
-// level's kinematics).  Values go to memory as they are formed and the loops
-// over parts stay rolled: this code shares the z-pass kernel's registers.
-__device__ inline void write_step(StateHdr* h, int p, const double* tot, const Coef& c, StepCtl ctl, double dx,
-                                  double eta, double* history, int ff, int rk) {
-    const Slot& sl = h->slot[p];
-    Slot& nx = h->slot[1 - p];
+// level's kinematics).  One value per thread: by one thread alone, value after
+// value from and to memory, it was the length of the z-pass on grids up to 96^3
+// (64^3 FP32 insect: 16.9 us with it, 13.5 without; a call's last step, without the
+// inverse transforms, 17.2 -> 7.9).
+__device__ inline void write_step(StateHdr* h, int p, const double* tot, const Coef& c, const StepCtl& ctl, double dx,
+                                  double eta, double* history, int ff, int rk, StepShared& w) {
+    const int tid = threadIdx.x;
+    const Slot& sl = w.sl;
+    const Kin& K = w.k;
     if (c.bad) {
-        h->status = c.bad;
+        if (tid == 0) h->status = c.bad;
         return;
     }
     const double dV = dx * dx * dx;
-    double* dg = h->diag;
-    const auto put = [&](int i, double v) {
-        dg[i] = v;
-        if (history) history[i] = v;
-    };
-    put(0, sl.t);
-    put(1, c.dt);
-    put(2, c.umax);
-    put(3, c.E);
     const bool corr = sl.have_I && sl.dt_prev > 0.0;
     // force (i < 3) or torque (i >= 3) on part k, with the unsteady term
     const auto part = [&](int k, int i) {
@@ -1598,107 +1602,88 @@ __device__ inline void write_step(StateHdr* h, int p, const double* tot, const C
         if (corr) v += (a[6 + i] * dV - sl.I_prev[k][i]) / sl.dt_prev;
         return v;
     };
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k)
-#pragma unroll 1
-        for (int i = 0; i < 6; ++i) put(4 + 6 * k + i, part(k, i));
-#pragma unroll 1
-    for (int i = 22; i < FLUSI_NDIAG; ++i) put(i, 0.0);
-    double J[3] = {0.0, 0.0, 0.0}, Ft[3] = {0.0, 0.0, 0.0}, mt[3] = {0.0, 0.0, 0.0};
-    if (ctl.body) {
-        const Kin& K = h->kin;
-#pragma unroll 1
-        for (int i = 0; i < 3; ++i) {
-            put(22 + i, K.xc[i]);
-            put(25 + i, K.uc[i]);
-            put(32 + i, K.omb[i]);
-        }
-#pragma unroll 1
-        for (int i = 0; i < 4; ++i) put(28 + i, K.eps[i]);
-        if (K.wings) {
-#pragma unroll 1
-            for (int s = 0; s < 2; ++s) {
-                double wg[3];
-                mat_tvec(K.Mb, K.omw[s], wg);
-                const double pa = -(part(1 + s, 3) * wg[0] + part(1 + s, 4) * wg[1] + part(1 + s, 5) * wg[2]);
-                put(35 + s, pa);
-                put(37 + s, K.pinert[s]);               // inertial power (Sec. 3.5)
-                put(39 + s, fmax(K.pinert[s] + pa, 0.0));  // total power, no energy storage
+    wg_copy8(&w.nx, &sl, (int)sizeof(Slot));
+    if (tid < FLUSI_NDIAG) {
+        double v = 0.0;
+        if (tid < 4) {
+            v = tid == 0 ? sl.t : (tid == 1 ? c.dt : (tid == 2 ? c.umax : c.E));
+        } else if (tid < 22) {
+            v = part((tid - 4) / 6, (tid - 4) % 6);
+        } else if (ctl.body) {
+            if (tid < 25) v = K.xc[tid - 22];
+            else if (tid < 28) v = K.uc[tid - 25];
+            else if (tid < 32) v = K.eps[tid - 28];
+            else if (tid < 35) v = K.omb[tid - 32];
+            else if (K.wings) {
+                const int s = (tid - 35) & 1;
+                if (tid >= 37 && tid < 39) {
+                    v = K.pinert[s];  // inertial power (Sec. 3.5)
+                } else {
+                    double wg[3];
+                    mat_tvec(K.Mb, K.omw[s], wg);
+                    const double pa = -(part(1 + s, 3) * wg[0] + part(1 + s, 4) * wg[1] + part(1 + s, 5) * wg[2]);
+                    v = tid < 37 ? pa : fmax(K.pinert[s] + pa, 0.0);  // total power, no energy storage
+                }
             }
         }
-        // moments about x_cntr: part sums moved from each part's reference point
-#pragma unroll 1
-        for (int k = 0; k < 3; ++k) {
-            const double* a = tot + 3 + 12 * k;
-            double r[3], F[3], IF[3], t1[3], t2[3];
-            for (int i = 0; i < 3; ++i) {
-                r[i] = K.xref[k][i] - K.xc[i];
-                F[i] = a[i] * dV / eta;
-                IF[i] = a[6 + i] * dV;
-                Ft[i] += part(k, i);
-            }
-            cross3(r, F, t1);
-            cross3(r, IF, t2);
-            for (int i = 0; i < 3; ++i) {
-                mt[i] += a[3 + i] * dV / eta + t1[i];
-                J[i] += a[9 + i] * dV + t2[i];
-            }
-        }
-        if (corr)
-            for (int i = 0; i < 3; ++i) mt[i] += (J[i] - sl.J_prev[i]) / sl.dt_prev;
+        h->diag[tid] = v;
+        if (history) history[tid] = v;
     }
-    {
-        static_assert(sizeof(Slot) % 8 == 0, "slot copy by words");
-        const double* src = reinterpret_cast<const double*>(&sl);
-        double* dst = reinterpret_cast<double*>(&nx);
-        constexpr int W = (int)(sizeof(Slot) / 8), B = 8;
-        static_assert(W % B == 0, "slot copy batches");
-#pragma unroll 1
-        for (int i = 0; i < W; i += B) {
-            double v[B];
-#pragma unroll
-            for (int j = 0; j < B; ++j) v[j] = src[i + j];
-#pragma unroll
-            for (int j = 0; j < B; ++j) dst[i + j] = v[j];
-        }
-    }
-    if (c.active) {
+    __syncthreads();
+    if (c.active && tid < 64) {
+        Slot& nx = w.nx;
         if (ctl.masked) {
-#pragma unroll 1
-            for (int k = 0; k < 3; ++k)
-#pragma unroll 1
-                for (int i = 0; i < 6; ++i) nx.I_prev[k][i] = tot[3 + 12 * k + 6 + i] * dV;
-            for (int i = 0; i < 3; ++i) nx.J_prev[i] = J[i];
-            nx.have_I = 1;
-        } else {
-            nx.have_I = 0;
+            if (tid < 18) nx.I_prev[tid / 6][tid % 6] = tot[3 + 12 * (tid / 6) + 6 + tid % 6] * dV;
         }
-        if (ff) {
-            // AB2 weights of the body (Euler on its first step)
-            double b1 = 1.0, b2 = 0.0;
-            if (sl.ff_have_prev) {
-                const double r = c.dt / sl.dt_prev;
-                b1 = 1.0 + 0.5 * r;
-                b2 = -0.5 * r;
+        if (tid >= 32 && tid < 35) {
+            // component i of the moments about x_cntr: part sums moved from each
+            // part's reference point
+            const int i = tid - 32, j = i == 2 ? 0 : i + 1, l = i == 0 ? 2 : i - 1;
+            double J = 0.0, Ft = 0.0, mt = 0.0;
+            if (ctl.body) {
+#pragma unroll 1
+                for (int k = 0; k < 3; ++k) {
+                    const double* a = tot + 3 + 12 * k;
+                    const double rj = K.xref[k][j] - K.xc[j], rl = K.xref[k][l] - K.xc[l];
+                    Ft += part(k, i);
+                    mt += a[3 + i] * dV / eta + (rj * (a[l] * dV / eta) - rl * (a[j] * dV / eta));
+                    J += a[9 + i] * dV + (rj * (a[6 + l] * dV) - rl * (a[6 + j] * dV));
+                }
+                if (corr) mt += (J - sl.J_prev[i]) / sl.dt_prev;
             }
-            nx.ff_w[0] = c.dt * b1;
-            nx.ff_w[1] = c.dt * b2;
-            for (int i = 0; i < 3; ++i) {
-                nx.ff_F[i] = Ft[i];
-                nx.ff_m[i] = mt[i];
+            if (ctl.masked) nx.J_prev[i] = J;
+            if (ff) {
+                nx.ff_F[i] = Ft;
+                nx.ff_m[i] = mt;
             }
-            nx.ff_state = 2;
-        } else {
-            nx.ff_state = 0;
-            nx.ff_have_prev = 0;
         }
-        nx.have_prev = rk ? 0 : 1;  // RK4 leaves no AB2 history (its stages use that storage)
-        nx.dt_prev = c.dt;
-        nx.t = sl.t + c.dt;
-        nx.n = sl.n + 1;
+        if (tid == 40) {
+            nx.have_I = ctl.masked ? 1 : 0;
+            if (ff) {
+                // AB2 weights of the body (Euler on its first step)
+                double b1 = 1.0, b2 = 0.0;
+                if (sl.ff_have_prev) {
+                    const double r = c.dt / sl.dt_prev;
+                    b1 = 1.0 + 0.5 * r;
+                    b2 = -0.5 * r;
+                }
+                nx.ff_w[0] = c.dt * b1;
+                nx.ff_w[1] = c.dt * b2;
+                nx.ff_state = 2;
+            } else {
+                nx.ff_state = 0;
+                nx.ff_have_prev = 0;
+            }
+            nx.have_prev = rk ? 0 : 1;  // RK4 leaves no AB2 history (its stages use that storage)
+            nx.dt_prev = c.dt;
+            nx.t = sl.t + c.dt;
+            nx.n = sl.n + 1;
+        }
     }
-    nx.rk_dt = c.active ? c.dt : 0.0;
-    h->cur = 1 - p;
+    if (tid == 41) w.nx.rk_dt = c.active ? c.dt : 0.0;
+    __syncthreads();
+    wg_copy8(&h->slot[1 - p], &w.nx, (int)sizeof(Slot));
+    if (tid == 0) h->cur = 1 - p;
 }
 
 // First level: workgroup b (< NRED) reduces the x-pass records
@@ -1808,18 +1793,42 @@ __device__ inline void reduce_scalars(const double* __restrict__ partial2, doubl
 // mask-block conversions run at once).
 constexpr int NT_KIN = 128;
 
+// The launch record of a single plan (and the device copy of its body
+// description) written by a workgroup from its kernel arguments, the record at
+// byte `at` of them and the description after it: read there by all threads in
+// parallel (as by-value arguments indexed by the thread they would go through
+// scratch memory; copied by one thread they took 8 us).
+static_assert(sizeof(Member) % 8 == 0 && alignof(Member) == 8 && alignof(flusi_insect) == 8,
+              "the record is followed by the description without a gap");
+__device__ __forceinline__ void member_write(Member* dst, void* ins, bool body, int at) {
+    const auto* ka = (const __attribute__((address_space(4))) unsigned long long*)__builtin_amdgcn_kernarg_segment_ptr() + at / 8;
+    constexpr int NM = (int)(sizeof(Member) / 8), NI = (int)(sizeof(flusi_insect) / 8);
+    auto* d = reinterpret_cast<unsigned long long*>(dst);
+    auto* e = static_cast<unsigned long long*>(ins);
+    for (int i = threadIdx.x; i < NM; i += blockDim.x) d[i] = ka[i];
+    if (body)
+        for (int i = threadIdx.x; i < NI; i += blockDim.x) e[i] = ka[NM + i];
+}
+static __global__ __launch_bounds__(NT_KIN) void k_member_set(Member* dst, Member v, flusi_insect) {
+    member_write(dst, const_cast<flusi_insect*>(v.ins), v.nc > 0, 8);
+}
+
 // Start of a stepping call, one workgroup per member: make slot 0 current and
-// evaluate the kinematics of the current time level.
+// evaluate the kinematics of the current time level.  A plan's own call (set)
+// first writes its launch record, the table's one entry; ensembles run the same
+// code on their table, so that members equal their solo runs bit for bit.
 template <typename T>
-static __global__ __launch_bounds__(NT_KIN) void k_prologue(const Member* __restrict__ mt, int nmem) {
-    if ((int)blockIdx.x >= nmem) return;
+static __global__ __launch_bounds__(NT_KIN) void k_prologue(Member* mt, long set, Member v, flusi_insect) {
+    if (set) {
+        member_write(mt, const_cast<flusi_insect*>(v.ins), v.nc > 0, 16);
+        __syncthreads();
+    }
     const Member& m = mt[blockIdx.x];
     StateHdr* hdr = m.hdr;
-    if (threadIdx.x == 0 && hdr->cur == 1) {
-        hdr->slot[0] = hdr->slot[1];
-        hdr->cur = 0;
-    }
+    const bool second = hdr->cur == 1;
+    if (second) wg_copy8(&hdr->slot[0], &hdr->slot[1], (int)sizeof(Slot));
     __syncthreads();
+    if (second && threadIdx.x == 0) hdr->cur = 0;
     __shared__ KinShared ks;
     if (m.nc > 0 && !hdr->status) kin_update<T>(m, 0, false, 0.0, ks);
 }
@@ -1855,22 +1864,11 @@ static __global__ void k_solid_set(StateHdr* h, Solid13 y) {
     }
 }
 
-// Writes the launch record of a single plan (and the device copy of its body
-// description) ahead of the kernels that read it, in stream order.
-static __global__ void k_member_set(Member* dst, Member v, flusi_insect ins) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *dst = v;
-        if (v.nc > 0) *const_cast<flusi_insect*>(v.ins) = ins;
-    }
-}
-
 static __global__ void k_hdr_init(StateHdr* hdr, double t0) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        unsigned char* b = reinterpret_cast<unsigned char*>(hdr);
-        for (size_t i = 0; i < sizeof(StateHdr); ++i) b[i] = 0;
-        hdr->slot[0].t = t0;
-        hdr->cur = 0;
-    }
+    auto* w = reinterpret_cast<unsigned*>(hdr);
+    for (int i = threadIdx.x; i < (int)(sizeof(StateHdr) / 4); i += blockDim.x) w[i] = 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) hdr->slot[0].t = t0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1932,8 +1930,9 @@ __global__ __launch_bounds__(nt_z(N, V)) void k_zpass(const Member* __restrict__
     constexpr int SC = cm_stride(N);
     constexpr int FB = zpass_fb<T, N>();
     constexpr int BUFB = FB * C * SC * (int)sizeof(cx<T>);
-    constexpr int REDB = nred_of(NX, N) * NV * 8;
-    __shared__ __align__(16) unsigned char smem[BUFB > REDB ? BUFB : REDB];
+    constexpr int REDB = (nred_of(NX, N) * NV * 8 + 15) / 16 * 16;
+    constexpr int WRB = STEPM ? REDB + (int)sizeof(StepShared) : 0;
+    __shared__ __align__(16) unsigned char smem[BUFB > WRB ? BUFB : WRB];
     __shared__ double tot[NV];
     __shared__ Coef cf;
     __shared__ cx<T> tws[N];
@@ -1970,10 +1969,12 @@ __global__ __launch_bounds__(nt_z(N, V)) void k_zpass(const Member* __restrict__
     if constexpr (STEPM) {
         if (tile == NBZ) {
             // the writer: every sum in the fixed order (diagnostics, forces)
+            StepShared& w = *reinterpret_cast<StepShared*>(smem + REDB);
+            wg_copy8(&w.sl, &hdr->slot[par], (int)sizeof(Slot));
+            wg_copy8(&w.k, &hdr->kin, (int)sizeof(Kin));
             reduce_level2<NTZ, nred_of(NX, N)>(partial2, reinterpret_cast<double*>(smem), tot);
-            if (tid == 0)
-                write_step(hdr, par, tot, step_coef(tot, hdr->slot[par], mb.ctl, dx, eta), mb.ctl, dx, eta,
-                           mb.history ? mb.history + (long)s * FLUSI_NDIAG : nullptr, mb.ff, mb.rk);
+            write_step(hdr, par, tot, step_coef(tot, w.sl, mb.ctl, dx, eta), mb.ctl, dx, eta,
+                       mb.history ? mb.history + (long)s * FLUSI_NDIAG : nullptr, mb.ff, mb.rk, w);
             return;
         }
         // column workgroups need max|u|^2 (order-free), the finiteness of the
