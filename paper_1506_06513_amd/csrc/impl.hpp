@@ -277,7 +277,6 @@ struct Impl final : ImplBase {
     static constexpr int K = G::K, KP = G::KP, M = G::M, Q = G::Q;
     static constexpr int KPp = G::KPp, Qp = G::Qp;
     static constexpr int C = cols_of(N, sizeof(cx<T>)), RW = rows_x(NX, sizeof(cx<T>)), NKX = NX / 2 + 1;
-    static constexpr int CZ = cols_z(N);
     static constexpr long N2 = (long)N * N, N3 = (long)NX * N * N;  // rows along x, points
     static constexpr long FULL = N2 * NKX;  // full-layout spectrum per field
 
@@ -307,9 +306,6 @@ struct Impl final : ImplBase {
 
     const CX* tw(const PlanData& p) const { return static_cast<const CX*>(p.tw); }
     const CX* twx(const PlanData& p) const { return static_cast<const CX*>(p.twx); }
-    // The z-pass runs as two launches (forward + update, then curl + inverse)
-    // when one fused launch would hold too many registers per thread.
-    static constexpr bool split_z() { return N >= 192; }
 
     // --- full-layout column passes ------------------------------------------------
     // column transforms of nf fields, 1D grid of nbx*nf workgroups
@@ -431,7 +427,6 @@ struct Impl final : ImplBase {
     static constexpr int nby(int nf) { return (N * KP + cols_of(N, sizeof(CX), V) - 1) / cols_of(N, sizeof(CX), V) * nf; }
     template <int V>
     static constexpr int nwg(int) { return (int)(N2 / xpass_wg_rows<T, NX, N>(V)); }
-    static constexpr int NBZ = (Q + CZ - 1) / CZ;  // z-pass tiles per member
     static int nwg_of(int v) { return v == 2 ? nwg<2>(0) : (v == 1 ? nwg<1>(0) : nwg<0>(0)); }
 
     // y-inverse of the 6 z-partial fields
@@ -494,9 +489,10 @@ struct Impl final : ImplBase {
     template <int MODE, int V, bool SP>
     static void zpass_launch(const GroupRun& g, const Member* mt, int nmem, int par, int s, int rk) {
         // modes with the reduction: one more workgroup per member (diagnostics, next level)
-        constexpr int nb = NBZ + ((MODE == MODE_STEP || MODE == MODE_STEP_LAST || MODE == MODE_RK1) ? 1 : 0);
+        constexpr int cz = zpass_cols<T, NX, N, MODE, V, SP>();
+        constexpr int nb = (Q + cz - 1) / cz + ((MODE == MODE_STEP || MODE == MODE_STEP_LAST || MODE == MODE_RK1) ? 1 : 0);
         if (nmem > 0)
-            k_zpass<T, NX, N, MODE, V, SP><<<(unsigned)(nb * nmem), nt_z(N, V), 0, g.stream>>>(
+            k_zpass<T, NX, N, MODE, V, SP><<<(unsigned)(nb * nmem), zpass_block<T, NX, N, MODE, V, SP>(), 0, g.stream>>>(
                 mt, static_cast<const CX*>(g.tw), par, s, rk);
     }
     // update modes: members without the sponge, then those with it (the table
@@ -520,8 +516,12 @@ struct Impl final : ImplBase {
     }
 
     Sched default_sched() const override {
+        // One z-pass launch everywhere (as two, update and inverse: 256^3 FP32 139 us
+        // against 130, FP64 245 against 226).  LDS tiles of 96 and 128 points with more
+        // threads per column (V = 0 / 1 / 2: 96^3 FP32 21.9 / 19.0 / 17.8 us, FP64 25.3 /
+        // 22.8 / 21.1; 128^3 FP32 29.4 / 23.0 / 21.3, FP64 35.6 / 29.7 / 36.4).
         Sched d;
-        d.split_z = split_z() ? 1 : 0;
+        d.z_pass = N == 96 ? 2 : (N == 128 ? (sizeof(T) < 8 ? 2 : 1) : 0);
         return d;
     }
 

@@ -67,6 +67,24 @@ __host__ __device__ constexpr int nt_z(int N, int V = 0) {
     if (V == 1) return t1;
     return fits(4 * t0) ? 4 * t0 : (fits(6 * t0) ? 6 * t0 : t1);
 }
+// The z-pass in registers (zpass_columns): grids from 192 to 512 points, without
+// the sponge and RK4, whose extra fields and stage sums would spill.  Smaller
+// grids have too few columns for a thread to hold 6 to 12 values of each field
+// (96^3 FP64 41 us against 21 with LDS tiles).  Columns per workgroup (V = 0): FP32
+// 8 up to 256^3 and 16 above, FP64 8, or 16 at 192^3; the other of the two with V =
+// 1, and 4 with V = 2, within 64 and 512 threads (V = 0 / 1 / 2: FP32 192^3 41 / 40 /
+// 52 us, 256^3 130 / 133 / 156, 384^3 518 / 547 / 774; FP64 192^3 97 / 100 / 117, 256^3
+// 226 / 238 / 251, 384^3 846 / 1089 / 941).
+__host__ __device__ constexpr int plan_z(int N, int cbytes) { return cbytes == 8 && N == 512 ? 1 : 0; }
+__host__ __device__ constexpr int lanes_z(int N, int cbytes) { return N / xr_E(N, plan_z(N, cbytes)); }
+__host__ __device__ constexpr int zregs_cols(int N, int cbytes, int V) {
+    const int G = lanes_z(N, cbytes);
+    const int c0 = cbytes == 8 ? (N <= 256 ? 8 : 16) : (N == 192 ? 16 : 8);
+    int c = V == 0 ? c0 : (V == 1 ? 24 - c0 : 4);
+    while (c * G > 512) c /= 2;
+    while (c * G < 64) c *= 2;
+    return c;
+}
 // Rows per workgroup of the x-pass: 3*RW*N ~ 3072 elements in LDS (V = 0), a
 // half (V = 1) or a quarter (V = 2) of that, at least 2 rows (an even count
 // pairs the rows' N_z in one forward transform); a single row where two rows
@@ -1897,9 +1915,10 @@ __host__ __device__ constexpr int zpass_fb() {
     return 3 * cols_z(N) * cm_stride(N) * (int)sizeof(cx<T>) <= 65536 ? 3 : 1;
 }
 
-template <typename T, int NX, int N, int MODE, int V, bool SP = false>
-__global__ __launch_bounds__(nt_z(N, V)) void k_zpass(const Member* __restrict__ mt, const cx<T>* __restrict__ tw,
-                                                      int par, int s, int rk) {
+// Columns in LDS tiles.
+template <typename T, int NX, int N, int MODE, int V, bool SP>
+__device__ __forceinline__ void zpass_tile(const Member* __restrict__ mt, const cx<T>* __restrict__ tw, int par, int s,
+                                           int rk) {
     using G = Geo<T, NX, N>;
     constexpr int K = G::K, KP = G::KP, M = G::M, Q = G::Q, Qp = G::Qp;
     constexpr int C = cols_z(N), NTZ = nt_z(N, V);
@@ -2234,6 +2253,288 @@ __global__ __launch_bounds__(nt_z(N, V)) void k_zpass(const Member* __restrict__
         }
         __syncthreads();
     }
+}
+
+// Columns in registers.  Thread (c, l) holds the elements of column c congruent to l
+// modulo G of each field before, between and after its transforms; LDS carries the
+// exchanges between butterfly stages only.
+// Bound: HBM from 256^3 on.  Measured per launch, the faster of the LDS tiles (one
+// launch or two) -> this: 192^3 FP32 53.5 -> 41 us, FP64 144 -> 97; 256^3 FP32 137 ->
+// 130 (512 MB, 4 TB/s; a large copy runs at 4.8), FP64 242 -> 226; 384^3 FP32 674 ->
+// 518, FP64 1011 -> 846; 512^3 FP32 949 -> 897, FP64 1781 -> 1686.
+template <typename T, int NX, int N, int MODE, int V>
+__device__ __forceinline__ void zpass_columns(const Member* __restrict__ mt, const cx<T>* __restrict__ tw, int par, int s) {
+    using G = Geo<T, NX, N>;
+    constexpr int K = G::K, KP = G::KP, M = G::M, Q = G::Q, Qp = G::Qp;
+    constexpr int PZ = plan_z(N, sizeof(cx<T>)), E = xr_E(N, PZ), GL = lanes_z(N, sizeof(cx<T>));
+    constexpr int C = zregs_cols(N, sizeof(cx<T>), V), NTZ = C * GL;
+    constexpr int NBZ = (Q + C - 1) / C;
+    // update modes: one more workgroup per member writes the diagnostics and
+    // the next time level, beside the column workgroups
+    constexpr bool STEPM = (MODE == MODE_STEP || MODE == MODE_STEP_LAST);
+    constexpr int NBZ1 = NBZ + (STEPM ? 1 : 0);
+    // state fields: [uhat 3][nold 3], each padded to 256 bytes
+    constexpr long fs_s = (((long)M * Qp * (long)sizeof(cx<T>) + 255) / 256 * 256) / (long)sizeof(cx<T>);
+    constexpr long fs_y = (long)N * Qp, fs_z = (long)N * Qp;
+    const int lin = xcd_tile(blockIdx.x, gridDim.x);
+    const Member& mb = mt[lin / NBZ1];
+    const int tile = lin % NBZ1;
+    StateHdr* hdr = mb.hdr;
+    glb<cx<T>>* uhat = gview(reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(hdr) + STATE_HDR_BYTES));
+    glb<cx<T>>* nold = uhat + 3 * fs_s;
+    const glb<cx<T>>* __restrict__ yin = gview(static_cast<const cx<T>*>(mb.bufB));
+    glb<cx<T>>* __restrict__ zout = gview(static_cast<cx<T>*>(mb.bufA));
+    const double kscale = mb.ks, nu = mb.nu, dx = mb.dx, eta = mb.eta;
+    const int mean_mode = mb.mean_mode;
+    const double* __restrict__ partial2 = mb.partial2;
+    constexpr int BUFB = C * xr_padded(N, PZ) * (int)sizeof(cx<T>);
+    constexpr int REDB = (nred_of(NX, N) * NV * 8 + 15) / 16 * 16;
+    constexpr int WRB = STEPM ? REDB + (int)sizeof(StepShared) : 0;
+    __shared__ __align__(16) unsigned char smem[BUFB > WRB ? BUFB : WRB];
+    __shared__ double tot[NV];
+    __shared__ Coef cf;
+    __shared__ cx<T> tws[N];
+    // AB2 steps: the integrating factors exp(-nu |k|^2 dt) split into the
+    // column's exp(-nu (kx^2 + ky^2) dt) and a table of exp(-nu kz^2 dt) over
+    // the kept kz (and the same for the previous step size)
+    __shared__ double exz[STEPM ? 2 : 1][STEPM ? M : 1];
+    cx<T>* buf = reinterpret_cast<cx<T>*>(smem);
+    if (*gview(&hdr->status)) return;
+    const int tid = threadIdx.x;
+    xr_twiddles<T, N, PZ>(tws, tw, NTZ);
+    const int c = tid % C, l = tid / C;
+    // threads past the last column repeat it and store nothing
+    const bool okq = tile * C + c < Q;
+    const int q = okq ? tile * C + c : Q - 1;
+    const int kxi = q % KP, myi = q / KP;
+    const double kxv = mb.ksx * kxi;
+    const double kyv = kscale * j_of_m(myi, K);
+
+    // place of element l of the thread's column in a row of a field; rows are at
+    // uniform bases
+    const unsigned oz = (unsigned)(((long)l * Qp + q) * (long)sizeof(cx<T>));
+    constexpr bool FWD = (MODE == MODE_IMPORT) || STEPM;
+    // forward input: a field's loads are in flight while the one before is
+    // transformed, the first one's together with the reduction loads
+    cx<T> v[E], vn[FWD ? E : 1];
+    const auto load_field = [&](int f) {
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            vn[t] = gld_at(yin + (f * fs_y + (long)(GL * t) * Qp), oz);
+        });
+    };
+    if constexpr (FWD) load_field(0);
+    if constexpr (STEPM) {
+        if (tile == NBZ) {
+            // the writer: every sum in the fixed order (diagnostics, forces)
+            StepShared& w = *reinterpret_cast<StepShared*>(smem + REDB);
+            wg_copy8(&w.sl, &hdr->slot[par], (int)sizeof(Slot));
+            wg_copy8(&w.k, &hdr->kin, (int)sizeof(Kin));
+            reduce_level2<NTZ, nred_of(NX, N)>(partial2, reinterpret_cast<double*>(smem), tot);
+            write_step(hdr, par, tot, step_coef(tot, w.sl, mb.ctl, dx, eta), mb.ctl, dx, eta,
+                       mb.history ? mb.history + (long)s * FLUSI_NDIAG : nullptr, mb.ff, mb.rk, w);
+            return;
+        }
+        // column workgroups need max|u|^2 (order-free), the finiteness of the
+        // |u|^2 sum and the non-finite flag: one wave, no LDS round trips
+        if (tid < 64) reduce_scalars<nred_of(NX, N)>(partial2, tot);
+        __syncthreads();
+        if (tid == 0) cf = step_coef(tot, hdr->slot[par], mb.ctl, dx, eta);
+        __syncthreads();
+        if (cf.bad) return;
+        if constexpr (STEPM) {
+            // visible after the barriers of the forward transforms
+            for (int m = tid; m < M; m += NTZ) {
+                const double kz = kscale * j_of_m(m, K);
+                exz[0][m] = exp(-nu * (kz * kz) * cf.dt);
+                exz[1][m] = cf.first ? 0.0 : exp(-nu * (kz * kz) * cf.dtp);
+            }
+        }
+    }
+    const bool active = STEPM ? (cf.active != 0) : true;
+    const bool do_fwd = (MODE == MODE_IMPORT) || (STEPM && active);
+    const bool do_inv = (MODE == MODE_STEP) || (MODE == MODE_INVERSE);
+
+    // the thread's kept modes: element l + GL t holds j_z = l + GL t, or that - N
+    // in the upper half, at storage row m.  Where only some lanes' elements are
+    // kept (xr_mode 2 and 4) the others read rows of other modes, all within the
+    // field (G <= K + 1), and neither store nor use what they form.
+    static_assert(GL <= K + 1, "rows of partly kept elements lie in the field");
+    cx<T> U[3][E];
+    const auto kept = [&](auto tc) {
+        constexpr int t = decltype(tc)::value, md = xr_mode(N, K, t, PZ);
+        return md == 1 || md == 3 || (md == 2 && l + GL * t <= K) || (md == 4 && l + GL * t >= N - K);
+    };
+    const auto jz_of = [&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        return xr_lane<GL>(l) + (xr_mode(N, K, t, PZ) >= 3 ? GL * t - N : GL * t);
+    };
+    const auto row_of = [](auto tc) {  // storage row of element 0 + GL t
+        constexpr int t = decltype(tc)::value;
+        return xr_mode(N, K, t, PZ) >= 3 ? GL * t - N + M : GL * t;
+    };
+    if (do_fwd) {
+        cx<T> Nh[3][E];
+        static_for<3>([&](auto fc) {
+            constexpr int f = decltype(fc)::value;
+            static_for<E>([&](auto tc) { v[decltype(tc)::value] = vn[decltype(tc)::value]; });
+            if (f < 2) load_field(f + 1);
+            xr_fft<T, N, -1, PZ, C, true>(v, buf + c, l, tws);
+            static_for<E>([&](auto tc) { Nh[f][decltype(tc)::value] = v[decltype(tc)::value]; });
+            // a workgroup of one exchange reads the buffer last
+            __syncthreads();
+        });
+        double dt = 0, b1 = 0, b2 = 0, dtp = 0;
+        int first = 1;
+        if (STEPM) {
+            dt = cf.dt;
+            b1 = cf.b1;
+            b2 = cf.b2;
+            dtp = cf.dtp;
+            first = cf.first;
+        }
+        double exy[2] = {0.0, 0.0};
+        if (STEPM) {
+            const double kxy2 = kxv * kxv + kyv * kyv;
+            exy[0] = exp(-nu * kxy2 * dt);
+            exy[1] = first ? 0.0 : exp(-nu * kxy2 * dtp);
+        }
+        // AB2: the old velocity and right-hand side of a mode
+        cx<T> uo[STEPM ? E : 1][3], no[STEPM ? E : 1][3];
+        const auto load_state = [&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            const long ru = (long)row_of(tc) * Qp;
+            static_for<3>([&](auto fc) {
+                constexpr int f = decltype(fc)::value;
+                uo[t][f] = gld_at<T>(uhat + (f * fs_s + ru), oz);
+                no[t][f] = gld_at<T>(nold + (f * fs_s + ru), oz);  // used after the first step
+            });
+        };
+        if constexpr (STEPM) load_state(std::integral_constant<int, 0>{});
+        static_for<E>([&](auto tc) {
+            constexpr int i = decltype(tc)::value;
+            // the next mode's loads go out before this one's stores (which may
+            // alias them as far as the compiler knows)
+            constexpr int nx = xr_next(N, K, i, PZ);
+            if constexpr (STEPM && xr_mode(N, K, i, PZ) != 0 && nx < E) load_state(std::integral_constant<int, nx>{});
+            if constexpr (xr_mode(N, K, i, PZ) != 0) {
+                const bool st = okq && kept(tc);
+                const double kzv = kscale * jz_of(tc);
+                const long ru = (long)row_of(tc) * Qp;  // uniform part of the place in a state field
+                const double k2 = kxv * kxv + kyv * kyv + kzv * kzv;
+                double nr[3], ni[3];
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    nr[f] = (double)Nh[f][i].x;
+                    ni[f] = (double)Nh[f][i].y;
+                }
+                if (k2 > 0.0) {
+                    const double ik2 = 1.0 / k2;
+                    const double sr = (kxv * nr[0] + kyv * nr[1] + kzv * nr[2]) * ik2;
+                    const double si = (kxv * ni[0] + kyv * ni[1] + kzv * ni[2]) * ik2;
+                    nr[0] -= kxv * sr; nr[1] -= kyv * sr; nr[2] -= kzv * sr;
+                    ni[0] -= kxv * si; ni[1] -= kyv * si; ni[2] -= kzv * si;
+                } else if (STEPM && mean_mode == FLUSI_MEAN_FIXED) {
+                    nr[0] = nr[1] = nr[2] = 0.0;
+                    ni[0] = ni[1] = ni[2] = 0.0;
+                }
+                if (MODE == MODE_IMPORT) {
+#pragma unroll
+                    for (int f = 0; f < 3; ++f) {
+                        U[f][i] = cx<T>{T(nr[f]), T(ni[f])};
+                        if (st) gst_at(uhat + (f * fs_s + ru), oz, U[f][i]);
+                    }
+                } else {
+                    const int m = STEPM ? l + row_of(tc) : 0;
+                    const double e1 = exy[0] * exz[0][m];
+                    const double c2 = first ? 0.0 : b2 * (exy[1] * exz[STEPM ? 1 : 0][m]);
+#pragma unroll
+                    for (int f = 0; f < 3; ++f) {
+                        double ar = nr[f], ai = ni[f];
+                        if (!first) {
+                            ar = b1 * nr[f] + c2 * (double)no[i][f].x;
+                            ai = b1 * ni[f] + c2 * (double)no[i][f].y;
+                        }
+                        const double vr = e1 * ((double)uo[i][f].x + dt * ar);
+                        const double vi = e1 * ((double)uo[i][f].y + dt * ai);
+                        U[f][i] = cx<T>{T(vr), T(vi)};
+                        if (st) gst_at(uhat + (f * fs_s + ru), oz, U[f][i]);
+                        if (st) gst_at(nold + (f * fs_s + ru), oz, cx<T>{T(nr[f]), T(ni[f])});
+                    }
+                }
+            }
+        });
+    } else if (do_inv) {
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if constexpr (xr_mode(N, K, t, PZ) != 0) {
+                const long ru = (long)row_of(tc) * Qp;
+                static_for<3>([&](auto fc) { U[decltype(fc)::value][t] = gld_at<T>(uhat + (decltype(fc)::value * fs_s + ru), oz); });
+            }
+        });
+    }
+    if (!do_inv) return;
+
+    const T kx = T(kxv), ky = T(kyv);
+    // u and w = i k x u
+    static_for<6>([&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        static_for<E>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            v[t] = cx<T>{T(0), T(0)};
+            if constexpr (xr_mode(N, K, t, PZ) != 0) {
+                cx<T> x;
+                if constexpr (g < 3) {
+                    x = U[g][t];
+                } else {
+                    const T kz = T(kscale * jz_of(tc));
+                    cx<T> a;
+                    if constexpr (g == 3) a = U[2][t] * ky - U[1][t] * kz;
+                    else if constexpr (g == 4) a = U[0][t] * kz - U[2][t] * kx;
+                    else a = U[1][t] * kx - U[0][t] * ky;
+                    x = mul_pi(a);
+                }
+                if (kept(tc)) v[t] = x;
+            }
+        });
+        if (g > 0 || !FWD) __syncthreads();
+        xr_fft<T, N, +1, PZ, C, true>(v, buf + c, l, tws);
+        if (okq) {
+            static_for<E>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                gst_at(zout + (g * fs_z + (long)(GL * t) * Qp), oz, v[t]);
+            });
+        }
+    });
+}
+
+template <typename T, int NX, int N, int MODE, bool SP>
+__host__ __device__ constexpr bool zregs_on() {
+    return N >= 192 && N <= 512 && !SP && MODE != MODE_RK1 && MODE != MODE_RKS;
+}
+template <typename T, int NX, int N, int MODE, int V, bool SP>
+__host__ __device__ constexpr int zpass_cols() {
+    if constexpr (zregs_on<T, NX, N, MODE, SP>()) return zregs_cols(N, sizeof(cx<T>), V);
+    else return cols_z(N);
+}
+template <typename T, int NX, int N, int MODE, int V, bool SP>
+__host__ __device__ constexpr int zpass_block() {
+    if constexpr (zregs_on<T, NX, N, MODE, SP>()) return zregs_cols(N, sizeof(cx<T>), V) * lanes_z(N, sizeof(cx<T>));
+    else return nt_z(N, V);
+}
+// waves per SIMD to compile for
+template <typename T, int NX, int N, int MODE, bool SP>
+__host__ __device__ constexpr int zpass_waves() {
+    if (!zregs_on<T, NX, N, MODE, SP>()) return 1;
+    if (sizeof(T) == 8) return xr_E(N) == 8 ? 2 : 1;
+    return xr_E(N) == 8 && plan_z(N, sizeof(cx<T>)) == 0 ? 3 : 2;
+}
+template <typename T, int NX, int N, int MODE, int V, bool SP = false>
+__global__ __launch_bounds__((zpass_block<T, NX, N, MODE, V, SP>()),
+                             (zpass_waves<T, NX, N, MODE, SP>())) void k_zpass(
+    const Member* __restrict__ mt, const cx<T>* __restrict__ tw, int par, int s, int rk) {
+    if constexpr (zregs_on<T, NX, N, MODE, SP>()) zpass_columns<T, NX, N, MODE, V>(mt, tw, par, s);
+    else zpass_tile<T, NX, N, MODE, V, SP>(mt, tw, par, s, rk);
 }
 
 // ---------------------------------------------------------------------------

@@ -20,7 +20,8 @@ namespace flusi {
 // 13.6 with 4; 48^3: 17.4 with 12, 14.8 with 6).  0: no plan (1152 points, whose
 // 32 lanes would hold 36 values per field).
 // Column plans (PLAN 1): one field per thread, so as few exchanges as the
-// radices allow.
+// radices allow.  (The z-pass, which keeps three fields of kept modes, takes row
+// plans but for 512 points in FP32.)
 __host__ __device__ constexpr int xr_E(int N, int PLAN = 0) {
     if (PLAN == 1) {
         switch (N) {
@@ -214,6 +215,12 @@ __host__ __device__ constexpr int xr_mode(int N, int K, int t, int PLAN = 0) {
     if (lo >= N - K) return 3;
     if (hi >= N - K) return 4;
     return 0;
+}
+
+// The next t after t that holds a kept mode on some lane (E: none).
+__host__ __device__ constexpr int xr_next(int N, int K, int t, int PLAN = 0) {
+    for (++t; t < xr_E(N, PLAN) && xr_mode(N, K, t, PLAN) == 0;) ++t;
+    return t;
 }
 
 }  // namespace flusi
