@@ -377,9 +377,11 @@ int flusi_pass_times(flusi_plan plan, double* ms, long long* launches);
  * Schedules and the autotuner.
  *
  * Each stepping pass (y-inverse, x-pass, y-forward, z-pass) exists in three
- * tile variants: 0 (default), 1 and 2 (y passes: a half / a quarter of the
- * columns per workgroup; x-pass: a half / a quarter of the rows, at least two;
- * z-pass: two or three / four or six times the threads per column).  The
+ * tile variants, 0, 1 and 2 (y passes: columns per workgroup, usually 16, twice
+ * or half as many; x-pass: wavefronts of rows per workgroup, two, four or one,
+ * and on rows of 1024 points or more its rows; z-pass: columns per workgroup or,
+ * on grids below 192, threads per column).  A new plan holds a schedule chosen
+ * for its grid and type.  The
  * z-pass runs either as one launch (update, curl and inverse z) or as two
  * (update, then curl + inverse z).  The velocity field does not depend on
  * the schedule (every variant performs the same operations per value); the

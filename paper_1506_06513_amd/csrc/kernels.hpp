@@ -30,8 +30,7 @@ constexpr int NV = 39;    // reduction values per workgroup (see xpass)
 constexpr int NRED_MAX = 64;  // most first-level reduction workgroups per member
 
 // Tile shapes.  Each stepping pass has NVARIANT shapes that compute the same
-// values (V = 0 the default); a schedule picks one per pass (see the
-// autotuner).
+// values; a schedule picks one per pass (see the autotuner).
 constexpr int NVARIANT = 3;
 // Columns per workgroup of the column passes (y, and z of the full layout): 16
 // (V = 0), which is 128 bytes of every row in FP32; in FP64 half of that (still 128
@@ -85,7 +84,8 @@ __host__ __device__ constexpr int zregs_cols(int N, int cbytes, int V) {
     while (c * G < 64) c *= 2;
     return c;
 }
-// Rows per workgroup of the x-pass: 3*RW*N ~ 3072 elements in LDS (V = 0), a
+// Rows per workgroup of the x-pass's LDS tiles (and pairs of rows of the real
+// transforms along x): 3*RW*N ~ 3072 elements in LDS (V = 0), a
 // half (V = 1) or a quarter (V = 2) of that, at least 2 rows (an even count
 // pairs the rows' N_z in one forward transform); a single row where two rows
 // of complex values (nine columns) would not fit the LDS (long FP64 rows),
@@ -2574,7 +2574,7 @@ __global__ __launch_bounds__(NT) void k_x_r2c(const T* __restrict__ in, cx<T>* _
 
 template <typename T, int N>
 __global__ __launch_bounds__(NT) void k_x_c2r(const cx<T>* __restrict__ in, T* __restrict__ out, long nrows, int nkx,
-                                              T scale, const cx<T>* __restrict__ tw) {
+                                              int pitch, T scale, const cx<T>* __restrict__ tw) {
     constexpr int RW = 2 * rows_x(N);
     constexpr int SC = cm_stride(N);
     constexpr int CP = RW / 2;
@@ -2586,8 +2586,8 @@ __global__ __launch_bounds__(NT) void k_x_c2r(const cx<T>* __restrict__ in, T* _
     for (int idx = tid; idx < CP * nkx; idx += NT) {
         const int p = idx / nkx, k = idx % nkx;
         const long ra = row0 + 2 * p, rb = ra + 1;
-        const cx<T> a = ra < nrows ? in[ra * nkx + k] : cx<T>{T(0), T(0)};
-        const cx<T> b = rb < nrows ? in[rb * nkx + k] : cx<T>{T(0), T(0)};
+        const cx<T> a = ra < nrows ? in[ra * pitch + k] : cx<T>{T(0), T(0)};
+        const cx<T> b = rb < nrows ? in[rb * pitch + k] : cx<T>{T(0), T(0)};
         if (k == 0 || 2 * k == N) {
             buf[lds_at<true, 1, SC>(k, p)] = cx<T>{a.x, b.x};
         } else {
