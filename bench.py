@@ -44,10 +44,12 @@ HBM_PEAK_GBS = 8000.0
 
 
 def x_rows(nx: int, cbytes: int, variant: int = 0) -> int:
-    """Rows per x-pass workgroup (the kernels' rows_x): 3*rows*nx ~ 3072 complex
-    values, halved per variant, at least 2, except one row where two rows of
-    nine columns would pass 150 KiB of LDS, or for the smaller variants of rows
-    of 1024 points or more."""
+    """Rows per record of partial sums in the byte model: the x-pass's LDS tiles
+    (the kernels' rows_x), 3*rows*nx ~ 3072 complex values, halved per variant,
+    at least 2, except one row where two rows of nine columns would pass 150 KiB
+    of LDS, or for the smaller variants of rows of 1024 points or more.  Rows of
+    up to 512 points go through another kernel, whose workgroups hold 1 to 32
+    rows; their records, a hundredth of the pass's bytes, are counted alike."""
     c, p = 1024 // nx, 2
     while p * 2 <= c:
         p *= 2
