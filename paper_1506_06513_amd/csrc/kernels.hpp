@@ -307,10 +307,16 @@ __global__ __launch_bounds__((nt_cols(N, sizeof(cx<T>)))) void k_colfft(const cx
                                       tile % nbx, tws, buf);
 }
 
+// Words that blocks of any members are copied by: as plain integers they would not
+// alias the members for the compiler, which may then move a member's load across
+// the copy, or take it for memory that no store of the kernel touches and read it
+// through the scalar cache, past stores still on their way.
+typedef unsigned long long __attribute__((may_alias)) word8;
+
 // nbytes (a multiple of 8; both ends 8-byte aligned) copied by the workgroup.
 __device__ __forceinline__ void wg_copy8(void* dst, const void* src, int nbytes) {
-    auto* d = static_cast<unsigned long long*>(dst);
-    const auto* q = static_cast<const unsigned long long*>(src);
+    auto* d = static_cast<word8*>(dst);
+    const auto* q = static_cast<const word8*>(src);
     for (int i = threadIdx.x; i < nbytes / 8; i += blockDim.x) d[i] = q[i];
 }
 
@@ -1815,33 +1821,40 @@ constexpr int NT_KIN = 128;
 // description) written by a workgroup from its kernel arguments, the record at
 // byte `at` of them and the description after it: read there by all threads in
 // parallel (as by-value arguments indexed by the thread they would go through
-// scratch memory; copied by one thread they took 8 us).
+// scratch memory; copied by one thread they took 8 us).  keep: a second copy of
+// the record for the workgroup itself (LDS), or null.
 static_assert(sizeof(Member) % 8 == 0 && alignof(Member) == 8 && alignof(flusi_insect) == 8,
               "the record is followed by the description without a gap");
-__device__ __forceinline__ void member_write(Member* dst, void* ins, bool body, int at) {
-    const auto* ka = (const __attribute__((address_space(4))) unsigned long long*)__builtin_amdgcn_kernarg_segment_ptr() + at / 8;
+__device__ __forceinline__ void member_write(Member* dst, Member* keep, void* ins, bool body, int at) {
+    const auto* ka = (const __attribute__((address_space(4))) word8*)__builtin_amdgcn_kernarg_segment_ptr() + at / 8;
     constexpr int NM = (int)(sizeof(Member) / 8), NI = (int)(sizeof(flusi_insect) / 8);
-    auto* d = reinterpret_cast<unsigned long long*>(dst);
-    auto* e = static_cast<unsigned long long*>(ins);
-    for (int i = threadIdx.x; i < NM; i += blockDim.x) d[i] = ka[i];
+    auto* d = reinterpret_cast<word8*>(dst);
+    auto* r = reinterpret_cast<word8*>(keep);
+    auto* e = static_cast<word8*>(ins);
+    for (int i = threadIdx.x; i < NM; i += blockDim.x) {
+        const word8 w = ka[i];
+        d[i] = w;
+        if (keep) r[i] = w;
+    }
     if (body)
         for (int i = threadIdx.x; i < NI; i += blockDim.x) e[i] = ka[NM + i];
 }
 static __global__ __launch_bounds__(NT_KIN) void k_member_set(Member* dst, Member v, flusi_insect) {
-    member_write(dst, const_cast<flusi_insect*>(v.ins), v.nc > 0, 8);
+    member_write(dst, nullptr, const_cast<flusi_insect*>(v.ins), v.nc > 0, 8);
 }
 
 // Start of a stepping call, one workgroup per member: make slot 0 current and
 // evaluate the kinematics of the current time level.  A plan's own call (set)
 // first writes its launch record, the table's one entry; ensembles run the same
-// code on their table, so that members equal their solo runs bit for bit.
+// code on their table, so that members equal their solo runs bit for bit.  The
+// workgroup works on a copy of the record in LDS, never on what it has just written
+// to memory.
 template <typename T>
 static __global__ __launch_bounds__(NT_KIN) void k_prologue(Member* mt, long set, Member v, flusi_insect) {
-    if (set) {
-        member_write(mt, const_cast<flusi_insect*>(v.ins), v.nc > 0, 16);
-        __syncthreads();
-    }
-    const Member& m = mt[blockIdx.x];
+    __shared__ Member m;
+    if (set) member_write(mt, &m, const_cast<flusi_insect*>(v.ins), v.nc > 0, 16);
+    else wg_copy8(&m, mt + blockIdx.x, (int)sizeof(Member));
+    __syncthreads();
     StateHdr* hdr = m.hdr;
     const bool second = hdr->cur == 1;
     if (second) wg_copy8(&hdr->slot[0], &hdr->slot[1], (int)sizeof(Slot));

@@ -1,0 +1,50 @@
+"""Properties of the generated gfx950 code (CPU: compiled here, read as assembly)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_1506_06513_amd.build import ARCH, CSRC, HIPCC_FLAGS, hipcc
+
+
+def _asm(tmp_path, text):
+    src = os.path.join(tmp_path, "unit.hip")
+    with open(src, "w") as f:
+        f.write(f'#include "{os.path.join(CSRC, "kernels.hpp")}"\n{text}\n')
+    out = os.path.join(tmp_path, "unit.s")
+    subprocess.run([hipcc(), *HIPCC_FLAGS, "-S", "--offload-device-only", src, "-o", out], check=True,
+                   capture_output=True, timeout=300)
+    return open(out).read()
+
+
+def _body(asm, name):
+    """Instructions of the kernel whose mangled name contains `name`."""
+    m = re.search(r"^(_ZN\S*" + name + r"\S*):.*?\n(.*?)^\s*s_endpgm", asm, re.M | re.S)
+    assert m, name
+    return [ln.split(";")[0].strip() for ln in m.group(2).splitlines()]
+
+
+def _foreign_scalar_loads(ins):
+    """Scalar loads from anything but the kernel arguments (s[0:1] on entry) and
+    constants of the code object (s_getpc)."""
+    known, out = {"s[0:1]"}, []
+    for line in ins:
+        op, _, rest = line.partition(" ")
+        args = [a.strip() for a in rest.split(",")]
+        if op == "s_mov_b64" and args[1] in known:
+            known.add(args[0])
+        elif op == "s_getpc_b64":
+            known.add(args[0])
+        elif op.startswith("s_load_") and args[1] not in known:
+            out.append(line)
+    return out
+
+
+@pytest.mark.parametrize("real", ["float", "double"])
+def test_prologue_reads_no_memory_through_the_scalar_cache(tmp_path, real):
+    # the prologue writes the launch record by vector stores and works on it: scalar
+    # loads of it would not wait for these stores and could return another record
+    asm = _asm(tmp_path, f"namespace flusi {{ template __global__ void k_prologue<{real}>(Member*, long, Member, "
+                         "flusi_insect); }")
+    assert _foreign_scalar_loads(_body(asm, "k_prologue")) == []
