@@ -22,6 +22,8 @@ HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # packed FP32 instructions are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # FMAs formed by the source's expressions alone, not by the code around them
+    "-ffp-contract=on",
     "-Wno-unused-result",
 ]
 

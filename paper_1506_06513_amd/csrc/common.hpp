@@ -35,11 +35,11 @@ template <typename T>
 __device__ __forceinline__ cx<T> operator+(cx<T> a, cx<T> b) { return {a.x + b.x, a.y + b.y}; }
 template <typename T>
 __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.x - b.x, a.y - b.y}; }
-template <typename T>
-__device__ __forceinline__ cx<T> operator*(cx<T> a, T s) { return {a.x * s, a.y * s}; }
-// The complex products name the product that each component rounds by itself:
-// left to the compiler's contraction, that choice depends on the code around the
-// call, and two tile variants of one pass then differ in the last bit.
+// Rounding.  The sources are compiled with -ffp-contract=on: a product and a sum of one
+// expression form an FMA, by the expression alone.  Left to contract as it sees fit
+// (the default), the compiler picks by the code around an expression, and tile
+// variants, launch forms or kernels that share it then differ in the last bit.
+// Products that operators keep from their sums are named as FMAs here.
 template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
     return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
@@ -48,6 +48,14 @@ __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
 template <typename T>
 __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {
     return {fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y))};
+}
+// a + b * s
+template <typename T>
+__device__ __forceinline__ cx<T> mul_add(cx<T> a, cx<T> b, T s) { return {fma(b.x, s, a.x), fma(b.y, s, a.y)}; }
+// a * s - b * t
+template <typename T>
+__device__ __forceinline__ cx<T> mul_diff(cx<T> a, T s, cx<T> b, T t) {
+    return {fma(a.x, s, -(b.x * t)), fma(a.y, s, -(b.y * t))};
 }
 template <typename T>
 __device__ __forceinline__ cx<T> conj(cx<T> a) { return {a.x, -a.y}; }

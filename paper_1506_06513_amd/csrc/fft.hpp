@@ -154,12 +154,12 @@ struct Dft<3, DIR, T> {
         constexpr T s3 = T(0.86602540378443864676372317075293618347);
         const cx<T> s = v[1] + v[2];
         const cx<T> d = v[1] - v[2];
-        const cx<T> m = v[0] - s * h;
+        const cx<T> m = mul_add(v[0], s, -h);
         // forward: X1 = m - i s3 d, X2 = m + i s3 d
-        const cx<T> r = (DIR < 0) ? mul_mi(d * s3) : mul_pi(d * s3);
+        const cx<T> r = (DIR < 0) ? mul_mi(d) : mul_pi(d);
         v[0] = v[0] + s;
-        v[1] = m + r;
-        v[2] = m - r;
+        v[1] = mul_add(m, r, s3);
+        v[2] = mul_add(m, r, -s3);
     }
 };
 

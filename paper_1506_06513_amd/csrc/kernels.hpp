@@ -2243,9 +2243,9 @@ __device__ __forceinline__ void zpass_tile(const Member* __restrict__ mt, const 
                         } else {
                             const T kz = T(kscale * j_of_m(m, K));
                             cx<T> a;
-                            if (g == 3) a = U[2][i] * ky - U[1][i] * kz;
-                            else if (g == 4) a = U[0][i] * kz - U[2][i] * kx;
-                            else a = U[1][i] * kx - U[0][i] * ky;
+                            if (g == 3) a = mul_diff(U[2][i], ky, U[1][i], kz);
+                            else if (g == 4) a = mul_diff(U[0][i], kz, U[2][i], kx);
+                            else a = mul_diff(U[1][i], kx, U[0][i], ky);
                             v = mul_pi(a);
                         }
                     }
@@ -2502,9 +2502,9 @@ __device__ __forceinline__ void zpass_columns(const Member* __restrict__ mt, con
                 } else {
                     const T kz = T(kscale * jz_of(tc));
                     cx<T> a;
-                    if constexpr (g == 3) a = U[2][t] * ky - U[1][t] * kz;
-                    else if constexpr (g == 4) a = U[0][t] * kz - U[2][t] * kx;
-                    else a = U[1][t] * kx - U[0][t] * ky;
+                    if constexpr (g == 3) a = mul_diff(U[2][t], ky, U[1][t], kz);
+                    else if constexpr (g == 4) a = mul_diff(U[0][t], kz, U[2][t], kx);
+                    else a = mul_diff(U[1][t], kx, U[0][t], ky);
                     x = mul_pi(a);
                 }
                 if (kept(tc)) v[t] = x;
@@ -2638,9 +2638,9 @@ __global__ void k_curl_full(const cx<T>* __restrict__ uh, cx<T>* __restrict__ ou
     out[e] = u0;
     out[tot + e] = u1;
     out[2 * tot + e] = u2;
-    out[3 * tot + e] = mul_pi(u2 * ky - u1 * kz);
-    out[4 * tot + e] = mul_pi(u0 * kz - u2 * kx);
-    out[5 * tot + e] = mul_pi(u1 * kx - u0 * ky);
+    out[3 * tot + e] = mul_pi(mul_diff(u2, ky, u1, kz));
+    out[4 * tot + e] = mul_pi(mul_diff(u0, kz, u2, kx));
+    out[5 * tot + e] = mul_pi(mul_diff(u1, kx, u0, ky));
 }
 
 // N = u x w - (chi/C_eta)(u - u_s) in place over the first three fields; max|u|^2 partials

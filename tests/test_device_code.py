@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from paper_1506_06513_amd.build import ARCH, CSRC, HIPCC_FLAGS, hipcc
+from paper_1506_06513_amd.build import CSRC, HIPCC_FLAGS, hipcc
 
 
 def _asm(tmp_path, text):
@@ -48,3 +48,13 @@ def test_prologue_reads_no_memory_through_the_scalar_cache(tmp_path, real):
     asm = _asm(tmp_path, f"namespace flusi {{ template __global__ void k_prologue<{real}>(Member*, long, Member, "
                          "flusi_insect); }")
     assert _foreign_scalar_loads(_body(asm, "k_prologue")) == []
+
+
+def test_no_rounding_is_left_to_the_code_around_an_expression(tmp_path):
+    # an operation flagged "contract" may or may not join an FMA, by its context: tile
+    # variants and launch forms of one pass would then differ in the last bit
+    out = os.path.join(tmp_path, "unit.ll")
+    subprocess.run([hipcc(), *HIPCC_FLAGS, "-DFLUSI_N=16", "-S", "-emit-llvm", "--offload-device-only",
+                    os.path.join(CSRC, "inst.hip"), "-o", out], check=True, capture_output=True, timeout=300)
+    flagged = [ln.strip() for ln in open(out) if re.search(r"= f(add|sub|mul) (\w+ )*contract ", ln)]
+    assert flagged == []
