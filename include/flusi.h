@@ -383,7 +383,8 @@ int flusi_pass_times(flusi_plan plan, double* ms, long long* launches);
  * on grids below 192, threads per column).  A new plan holds a schedule chosen
  * for its grid and type.  The
  * z-pass runs either as one launch (update, curl and inverse z) or as two
- * (update, then curl + inverse z).  The velocity field does not depend on
+ * (update, then curl + inverse z), with the vorticity sponge always as two from
+ * 192 points on.  The velocity field does not depend on
  * the schedule (every variant performs the same operations per value); the
  * x-pass variant changes only the summation order of the FP64 diagnostic
  * integrals (energy, force, torque), at round-off level.

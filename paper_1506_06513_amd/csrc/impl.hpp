@@ -495,15 +495,40 @@ struct Impl final : ImplBase {
             k_zpass<T, NX, N, MODE, V, SP><<<(unsigned)(nb * nmem), zpass_block<T, NX, N, MODE, V, SP>(), 0, g.stream>>>(
                 mt, static_cast<const CX*>(g.tw), par, s, rk);
     }
+    // The inverse z transform runs in the update's launch or in one of its own (the
+    // first of every call, and of every step with split_z).  Both have to be of one
+    // form, registers or LDS tiles, whose radix plans round differently: else a
+    // member's velocity would depend on the schedule and on the calls its steps come
+    // in.  From 192 to 512 points the separate launch is the register form.  RK4's
+    // updates are tiles with their inverse, so RK4 runs take its tile form (SP
+    // selects it).  The sponge's updates are tiles too; from 192 points on they
+    // never hold the inverse, whatever split_z says: their nine transforms and the
+    // inverse's six together were the slower way (a step in one launch / in two: 192^3
+    // FP32 258 / 240 us, FP64 525 / 485; 384^3 2205 / 1973, 4118 / 4069; 512^3 4644 / 4259,
+    // 8235 / 7885; 1152x768x768 FP64 85.7 / 81.1 ms, FP32 41.8 / 41.9; only 256^3
+    // loses, 568 / 584, 972 / 982).
+    static constexpr bool SP_TWO = N >= 192;
+    static constexpr bool INV_REGS = zregs_on<T, NX, N, MODE_INVERSE, false>();
     // update modes: members without the sponge, then those with it (the table
     // is ordered that way); other modes: all members in one launch
     template <int MODE, int V>
     static void zpass_v(const GroupRun& g, int par, int s, int rk) {
         constexpr bool update = MODE == MODE_STEP || MODE == MODE_STEP_LAST || MODE == MODE_RK1 || MODE == MODE_RKS;
-        const int nsp = g.n_nc[1][0] + g.n_nc[1][1] + g.n_nc[1][2];
+        const int nsp = g.n_nc[1][0] + g.n_nc[1][1] + g.n_nc[1][2], n0 = g.nmem - nsp;
+        if constexpr (MODE == MODE_INVERSE && INV_REGS) {
+            if (g.rk) {
+                zpass_launch<MODE, V, true>(g, g.mt, g.nmem, par, s, rk);
+                return;
+            }
+        }
         if (update && nsp) {
-            zpass_launch<MODE, V, false>(g, g.mt, g.nmem - nsp, par, s, rk);
-            zpass_launch<MODE, V, update>(g, g.mt + (g.nmem - nsp), nsp, par, s, rk);
+            zpass_launch<MODE, V, false>(g, g.mt, n0, par, s, rk);
+            if constexpr (MODE == MODE_STEP && SP_TWO) {
+                zpass_launch<MODE_STEP_LAST, V, true>(g, g.mt + n0, nsp, par, s, rk);
+                zpass_launch<MODE_INVERSE, V, false>(g, g.mt + n0, nsp, par, s, rk);
+            } else {
+                zpass_launch<MODE, V, update>(g, g.mt + n0, nsp, par, s, rk);
+            }
         } else {
             zpass_launch<MODE, V, false>(g, g.mt, g.nmem, par, s, rk);
         }
