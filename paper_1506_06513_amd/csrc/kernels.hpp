@@ -2555,8 +2555,15 @@ __global__ __launch_bounds__((zpass_block<T, NX, N, MODE, V, SP>()),
 // packed into one complex transform.  nkx: number of kx written/read
 // (n/2+1 for the full layout, K+1 for the pruned import).
 // ---------------------------------------------------------------------------
+// Waves per SIMD to compile the forward transform for: five in FP64 with 16 values per
+// lane, which 96 registers allow; the compiler's own choice of 98 leaves four (256^3
+// FP64, three fields: 241 us, 204 with five).
 template <typename T, int N>
-__global__ __launch_bounds__(NT) void k_x_r2c(const T* __restrict__ in, cx<T>* __restrict__ out, long nrows, int nkx,
+__host__ __device__ constexpr int xr2c_waves() {
+    return sizeof(T) == 8 && N >= 128 && fft_E(N) == 16 ? 5 : 1;
+}
+template <typename T, int N>
+__global__ __launch_bounds__(NT, (xr2c_waves<T, N>())) void k_x_r2c(const T* __restrict__ in, cx<T>* __restrict__ out, long nrows, int nkx,
                                               int pitch, const cx<T>* __restrict__ tw) {
     constexpr int RW = 2 * rows_x(N);  // real rows per workgroup
     constexpr int SC = cm_stride(N);

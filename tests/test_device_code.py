@@ -50,6 +50,17 @@ def test_prologue_reads_no_memory_through_the_scalar_cache(tmp_path, real):
     assert _foreign_scalar_loads(_body(asm, "k_prologue")) == []
 
 
+@pytest.mark.parametrize("n", [128, 256])
+def test_forward_real_transform_leaves_room_for_five_waves(tmp_path, n):
+    # 512 vector registers per lane and SIMD, in steps of 8: five waves take 96 at most
+    asm = _asm(tmp_path, f"namespace flusi {{ template __global__ void k_x_r2c<double, {n}>(const double*, "
+                         "cx<double>*, long, int, int, const cx<double>*); }")
+    meta = asm[asm.index(".amdgpu_metadata"):]
+    entry = next(e for e in meta.split("  - .agpr_count") if "k_x_r2c" in e)
+    assert int(re.search(r"\.vgpr_count:\s+(\d+)", entry).group(1)) <= 96
+    assert int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", entry).group(1)) == 0
+
+
 def test_no_rounding_is_left_to_the_code_around_an_expression(tmp_path):
     # an operation flagged "contract" may or may not join an FMA, by its context: tile
     # variants and launch forms of one pass would then differ in the last bit
