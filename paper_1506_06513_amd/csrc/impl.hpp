@@ -541,12 +541,16 @@ struct Impl final : ImplBase {
     }
 
     Sched default_sched() const override {
-        // One z-pass launch everywhere (as two, update and inverse: 256^3 FP32 139 us
-        // against 130, FP64 245 against 226).  LDS tiles of 96 and 128 points with more
-        // threads per column (V = 0 / 1 / 2: 96^3 FP32 21.9 / 19.0 / 17.8 us, FP64 25.3 /
-        // 22.8 / 21.1; 128^3 FP32 29.4 / 23.0 / 21.3, FP64 35.6 / 29.7 / 36.4).
+        // One z-pass launch (as two, update and inverse: 256^3 FP32 139 us against 130,
+        // FP64 245 against 226; 1152x768x768 34.6 ms per step against 34.5, FP64 46.3
+        // against 46.2).  Tile variants: the first from 192 points on (zregs_cols); the
+        // LDS tiles of smaller grids with the most threads per column, but for FP64 at
+        // 128 points, the largest of these tiles (us per step of a sphere, V = 0 / 1 / 2:
+        // 16 points FP32 22.0 / 20.9 / 20.4, 32 FP64 24.4 / 23.4 / 23.4, 64 FP32 32.7 / 30.3 /
+        // 29.6, FP64 43.8 / 41.3 / 40.0, 96 FP64 76.6 / 73.8 / 72.6, 128 FP32 73.6 / 65.5 / 63.8,
+        // FP64 107.2 / 100.4 / 108.1; RK4 64 FP32 138 / 124 / 112, 128 FP64 437 / 400 / 429).
         Sched d;
-        d.z_pass = N == 96 ? 2 : (N == 128 ? (sizeof(T) < 8 ? 2 : 1) : 0);
+        d.z_pass = N >= 192 ? 0 : (N == 128 && sizeof(T) == 8 ? 1 : 2);
         return d;
     }
 
