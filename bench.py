@@ -44,12 +44,10 @@ HBM_PEAK_GBS = 8000.0
 
 
 def x_rows(nx: int, cbytes: int, variant: int = 0) -> int:
-    """Rows per record of partial sums in the byte model: the x-pass's LDS tiles
-    (the kernels' rows_x), 3*rows*nx ~ 3072 complex values, halved per variant,
-    at least 2, except one row where two rows of nine columns would pass 150 KiB
-    of LDS, or for the smaller variants of rows of 1024 points or more.  Rows of
-    up to 512 points go through another kernel, whose workgroups hold 1 to 32
-    rows; their records, a hundredth of the pass's bytes, are counted alike."""
+    """Rows per x-pass workgroup of the kernels' LDS tiles (their rows_x):
+    3*rows*nx ~ 3072 complex values, halved per variant, at least 2, except one row
+    where two rows of nine columns would pass 150 KiB of LDS, or for the smaller
+    variants of rows of 1024 points or more."""
     c, p = 1024 // nx, 2
     while p * 2 <= c:
         p *= 2
@@ -61,7 +59,29 @@ def x_rows(nx: int, cbytes: int, variant: int = 0) -> int:
     return p
 
 
-def pass_bytes(n: int, cbytes: int, split_z: bool, x_variant: int = 0, nx: int | None = None) -> dict:
+def x_wg_rows(nx: int, n: int, cbytes: int, variant: int) -> int:
+    """Rows per x-pass workgroup of a tile variant (the kernels' xpass_wg_rows): rows
+    of up to 512 points go in registers, E values per lane, 64 E / nx rows (or
+    pairs) per wavefront and 4, 2 or 1 wavefronts with rows per workgroup; longer
+    rows in LDS tiles.  Each workgroup leaves one record of 39 sums."""
+    if nx > 512:
+        return x_rows(nx, cbytes, variant)
+    e = {16: 4, 24: 6, 32: 4, 48: 6, 64: 4, 96: 12, 128: 8, 192: 12, 256: 8, 384: 12, 512: 8}[nx]
+    wide, share = cbytes > 8, nx <= 128
+    rows = 64 * e // nx * (1 if share or (wide and e <= 8) else 2)
+    if share:
+        w = 2 if wide and e > 8 else 4
+        while w > 1 and n * n // (w * rows) < 256:
+            w //= 2
+        w = max(1, w >> variant)
+    else:
+        w = 2 if variant == 0 or (variant == 1 and wide and e > 8) else (4 if variant == 1 else 1)
+    while n * n % (w * rows):
+        w //= 2
+    return w * rows
+
+
+def pass_bytes(n: int, cbytes: int, split_z: bool, x_variant: int | None = None, nx: int | None = None) -> dict:
     """Algorithmic HBM bytes per launch of each pass of the pruned schedule on
     an nx x n x n grid (nx = n by default).
 
@@ -69,13 +89,15 @@ def pass_bytes(n: int, cbytes: int, split_z: bool, x_variant: int = 0, nx: int |
     z-partials [6][n][Q], y-partials [6][n][n][KP], x-output [3][n][n][KP],
     y-output [3][n][Q], state u_hat and previous right-hand side [3][M][Q] each.
     z_pass is forward z + projection + AB2 (+ curl and inverse z when fused);
-    z_inverse is curl + inverse z from the state."""
+    z_inverse is curl + inverse z from the state.  x_variant: the x-pass's tile
+    variant, whose workgroups' records of sums are counted; None: one record per
+    x_rows rows, whatever the schedule."""
     nx = n if nx is None else nx
     K = (n - 1) // 3
     KP, M = (nx - 1) // 3 + 1, 2 * K + 1
     Q = M * KP
     s = cbytes
-    nwg = n * n // x_rows(nx, cbytes, x_variant)
+    nwg = n * n // (x_rows(nx, cbytes) if x_variant is None else x_wg_rows(nx, n, cbytes, x_variant))
     zup = (3 * n * Q + 4 * 3 * M * Q) * s
     return {
         "z_inverse": (3 * M * Q + 6 * n * Q) * s,
