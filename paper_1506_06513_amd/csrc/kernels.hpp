@@ -610,29 +610,6 @@ __device__ __forceinline__ double wave_max(double v) {
                             __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
-// Reduce NV per-thread values (value 0 and 2 by max, the rest by sum) over the
-// workgroup; the result lands in out[0..NV) (global) from thread v.
-template <int NVAL>
-__device__ __forceinline__ void block_reduce_store(const double (&acc)[NVAL], double (*red)[NV], double* out) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int v = 0; v < NVAL; ++v) {
-        double r = 0.0;
-        if (__any(acc[v] != 0.0)) r = (v == 0 || v == 2) ? wave_max(acc[v]) : wave_sum(acc[v]);
-        if (lane == 0) red[wv][v] = r;
-    }
-    __syncthreads();
-    const int t = threadIdx.x;
-    if (t < NV) {
-        double r = 0.0;
-        if (t < NVAL) {
-            r = red[0][t];
-            for (int w = 1; w < NT / 64; ++w) r = (t == 0 || t == 2) ? fmax(r, red[w][t]) : r + red[w][t];
-        }
-        gview(out)[t] = r;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // x-pass: inverse x, pointwise source with the mask, FP64 partial sums,
 // forward x, by the row kernel (xpass_rows), or for rows of 1024 points or more by
@@ -719,35 +696,30 @@ __host__ __device__ constexpr int xpass_waves() {
 }
 
 // Conservative test of which points of a row can have chi > 0, so that the mask
-// itself is evaluated with such points in neighbouring lanes.  Rows 0..2 of aff:
-// the body frame's coordinates as affine functions of the global ones (three
-// coefficients and a constant) and the half-widths beyond which the thorax's
-// chi is 0; rows 3..5 and 6..8: the same of the wings' frames about their
+// itself is evaluated with such points in neighbouring lanes.  Rows 0 and 1 of aff:
+// the body frame's y and z as affine functions of the global coordinates (three
+// coefficients and a constant) and the half-width beyond which the thorax's
+// chi is 0; rows 2..4 and 5..7: the coordinates of the wings' frames about their
 // outlines' centres (an ellipse's delta exceeds thr where |e_x| > A + thr, as
 // the overshoot beyond the outline along the ray from the centre is at least
 // its x component).  The half-widths carry a margin far above the rounding.
+constexpr int MASK_FRAMES = 8;
 template <typename T>
 __device__ __forceinline__ void mask_frames(const KinT<T>& k, T side, T* aff, int r) {
-    const int w = r / 3 - 1, i = r % 3;
-    T c[3], o = T(0), h;
-    if (r < 3) {
-        for (int q = 0; q < 3; ++q) c[q] = k.Mb[3 * i + q];
-        h = i == 0 ? k.ea : k.eb;
-    } else {
-        const T* M = k.Mws[w] + 3 * i;
-        for (int q = 0; q < 3; ++q) c[q] = M[0] * k.Mb[q] + M[1] * k.Mb[3 + q] + M[2] * k.Mb[6 + q];
-        o = -(M[0] * k.piv[w][0] + M[1] * k.piv[w][1] + M[2] * k.piv[w][2]);
-        const bool poly = k.wshape == FLUSI_WING_FOURIER;
-        if (i == 0) {
-            o -= k.wcx;
-            h = poly ? k.wrad : k.wA;
-        } else if (i == 1) {
-            o -= k.wcy;
-            h = poly ? k.wrad : k.wB;
-        } else {
-            h = T(0.5) * k.wt;
-        }
+    const bool body = r < 2, right = r >= 5;
+    const int i = body ? r + 1 : (right ? r - 5 : r - 2);  // axis of its frame
+    const int w = right ? 1 : 0;
+    const T* M = k.Mws[w] + 3 * i;
+    const T hc = k.wshape == FLUSI_WING_FOURIER ? k.wrad : (i == 0 ? k.wA : k.wB);
+    const T hw = i == 2 ? T(0.5) * k.wt : hc;
+    const T e = i == 2 ? T(0) : (i == 0 ? k.wcx : k.wcy);  // the outline's centre
+    const T ow = -(M[0] * k.piv[w][0] + M[1] * k.piv[w][1] + M[2] * k.piv[w][2]) - e;
+    T c[3];
+    for (int q = 0; q < 3; ++q) {
+        const T cw = M[0] * k.Mb[q] + M[1] * k.Mb[3 + q] + M[2] * k.Mb[6 + q], cb = k.Mb[3 * i + q];
+        c[q] = body ? cb : cw;
     }
+    const T o = body ? T(0) : ow, h = body ? k.eb : hw;
     const T oc = c[0] * k.xc[0] + c[1] * k.xc[1] + c[2] * k.xc[2];
     const T sc = side + fabs(k.xc[0]) + fabs(k.xc[1]) + fabs(k.xc[2]) + fabs(o);
     for (int q = 0; q < 3; ++q) aff[5 * r + q] = c[q];
@@ -764,8 +736,8 @@ __device__ __forceinline__ unsigned mask_candidates(const KinT<T>& k, const T* a
     const T x0 = dx * T(l), dg = dx * T(G);
     const T xc = k.xc[0], rb = k.r2b * T(1.0 + 1e-5);
     if (k.body == FLUSI_BODY_ELLIPSOID && !k.nsph) {
-        const T y0 = aff[6] * y + aff[7] * z + aff[8], z0 = aff[11] * y + aff[12] * z + aff[13];
-        const T y1 = aff[5], z1 = aff[10], h = aff[9] > aff[14] ? aff[9] : aff[14];
+        const T y0 = aff[1] * y + aff[2] * z + aff[3], z0 = aff[6] * y + aff[7] * z + aff[8];
+        const T y1 = aff[0], z1 = aff[5], h = aff[4] > aff[9] ? aff[4] : aff[9];
 #pragma unroll
         for (int t = 0; t < E; ++t) {
             const T x = x0 + dg * T(t), d = x - xc, a = y0 + y1 * x, b = z0 + z1 * x;
@@ -782,7 +754,7 @@ __device__ __forceinline__ unsigned mask_candidates(const KinT<T>& k, const T* a
         if (k.wings) {
 #pragma unroll 1
             for (int w = 0; w < 2; ++w) {
-                const T* f = aff + 15 + 15 * w;
+                const T* f = aff + 10 + 15 * w;
                 const T p0 = f[1] * y + f[2] * z + f[3], q0 = f[6] * y + f[7] * z + f[8], s0 = f[11] * y + f[12] * z + f[13];
                 const T p1 = f[0], q1 = f[5], s1 = f[10], ph = f[4], qh = f[9], sh = f[14];
 #pragma unroll
@@ -827,15 +799,16 @@ __device__ __forceinline__ void xpass_rows(const Member& m, const cx<T>* __restr
     constexpr size_t LB = NC > 0 ? 3 * sizeof(T) * CAP + sizeof(unsigned short) * CAP : 0;
     constexpr size_t WB = ((XB > LB ? XB : LB) + 15) / 16 * 16;
     __shared__ __align__(16) unsigned char lds[R * WB];
-    // N_z (and chi_sp w_z) of the first row of two, kept for the transform that
-    // the second shares with it
-    __shared__ T nzl[P == 2 ? R * CAP : 1], szl[P == 2 && SP ? R * CAP : 1];
+    // N_z of the first row of two, kept for the transform that the second shares
+    // with it
+    static_assert(P == 1 || !SP, "with the sponge rows are transformed one by one");
+    __shared__ T nzl[P == 2 ? R * CAP : 1];
     __shared__ int counts[SHARE ? R : 1];  // points near the body of each wavefront's rows
     __shared__ double wred[W][NVAL];
     __shared__ KinT<T> kin;
     __shared__ cx<T> tws[NX];
     __shared__ typename std::conditional<K64, KinT<double>, char>::type kin64;
-    __shared__ T aff[NC > 0 ? 45 : 1];
+    __shared__ T aff[NC > 0 ? 5 * MASK_FRAMES : 1];
     const StateHdr* __restrict__ hdr = m.hdr;
     if (*gview(&hdr->status)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -867,7 +840,7 @@ __device__ __forceinline__ void xpass_rows(const Member& m, const cx<T>* __restr
     if (lane < NVAL) wred[wv][lane] = 0.0;
     __syncthreads();
     if constexpr (NC > 0) {
-        if (tid < 9) mask_frames(kin, T(dx * (NX > N ? NX : N)), aff, tid);
+        if (tid < MASK_FRAMES) mask_frames(kin, T(dx * (NX > N ? NX : N)), aff, tid);
         __syncthreads();
     }
     const KinT<double>* k64p = nullptr;
@@ -1122,12 +1095,10 @@ __device__ __forceinline__ void xpass_rows(const Member& m, const cx<T>* __restr
         if constexpr (SP) forward(z[1], o + 3 * fs, o + 4 * fs, true);
         // ... and of the rows' N_z (chi_sp w_z)
         T* keep = nzl + (P == 2 ? wv * CAP + lane : 0);
-        T* skeep = szl + (P == 2 && SP ? wv * CAP + lane : 0);
         if (P == 2 && p == 0) {
             static_for<E>([&](auto tc) {
                 constexpr int t = decltype(tc)::value;
                 keep[t * 64] = z[2][t].x;
-                if constexpr (SP) skeep[t * 64] = z[2][t].y;
             });
         } else {
             o = xout + 2 * fs + (long)row0 * KPp;
@@ -1140,9 +1111,9 @@ __device__ __forceinline__ void xpass_rows(const Member& m, const cx<T>* __restr
             if constexpr (SP) {
                 static_for<E>([&](auto tc) {
                     constexpr int t = decltype(tc)::value;
-                    v[t] = P == 2 ? cx<T>{skeep[t * 64], z[2][t].y} : cx<T>{z[2][t].y, T(0)};
+                    v[t] = cx<T>{z[2][t].y, T(0)};
                 });
-                forward(v, o + 3 * fs, o + 3 * fs + NG * KPp, P == 2);
+                forward(v, o + 3 * fs, o + 3 * fs, false);
             }
         }
     }
@@ -1314,7 +1285,8 @@ __device__ __forceinline__ void xpass_tile(const Member* __restrict__ mt, const 
     // Sweep index g -> (row r, x index i).  Each wave takes a compact patch of
     // PR rows x PX points (PR*PX = 64) rather than 64 points of one row, so the
     // lanes that need the mask's geometry tend to share waves.
-    constexpr int PR = (RW >= 4 && NX % 16 == 0) ? 4 : ((RW >= 2 && NX % 32 == 0) ? 2 : 1);
+    static_assert(RW <= 2, "tiles of rows of 1024 points or more");
+    constexpr int PR = (RW == 2 && NX % 32 == 0) ? 2 : 1;
     constexpr int PX = 64 / PR;
     const auto decode = [](int g, int& r, int& i) {
         if constexpr (PR == 1) {
@@ -2355,13 +2327,11 @@ __device__ __forceinline__ void zpass_columns(const Member* __restrict__ mt, con
         if (tid == 0) cf = step_coef(tot, hdr->slot[par], mb.ctl, dx, eta);
         __syncthreads();
         if (cf.bad) return;
-        if constexpr (STEPM) {
-            // visible after the barriers of the forward transforms
-            for (int m = tid; m < M; m += NTZ) {
-                const double kz = kscale * j_of_m(m, K);
-                exz[0][m] = exp(-nu * (kz * kz) * cf.dt);
-                exz[1][m] = cf.first ? 0.0 : exp(-nu * (kz * kz) * cf.dtp);
-            }
+        // visible after the barriers of the forward transforms
+        for (int m = tid; m < M; m += NTZ) {
+            const double kz = kscale * j_of_m(m, K);
+            exz[0][m] = exp(-nu * (kz * kz) * cf.dt);
+            exz[1][m] = cf.first ? 0.0 : exp(-nu * (kz * kz) * cf.dtp);
         }
     }
     const bool active = STEPM ? (cf.active != 0) : true;
