@@ -15,8 +15,8 @@
  *  - Box: n points per axis on y and z (side L) and nx on x (side L*nx/n),
  *    one spacing L/n, grid points x_i = i*L/n.  Cubic grids (nx = n) for n in
  *    16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512 (even and of the form
- *    2^a 3^b); boxes 48x32x32, 64x32x32 and 192x128x128 (see
- *    flusi_plan_create).
+ *    2^a 3^b); boxes 48x32x32, 64x32x32, 192x128x128, 1152x32x32 and
+ *    1152x768x768 (see flusi_plan_create).
  *  - Physical fields: [field][z][y][x] row-major, x fastest, real type of the
  *    plan (float for FLUSI_F32, double for FLUSI_F64).
  *  - Spectral fields, full layout: [field][kz][ky][kx] with kx = 0..nx/2
@@ -203,7 +203,8 @@ const char* flusi_last_error(void);
  * L/n on every axis: L is the side along y and z, the side along x is
  * L*nx/n (the non-cubic box of Sec. 4 and 6, 6x4x4 at 1152x768x768, has one
  * spacing).  Grids: the cubic n^3 for n in {16, 24, 32, 48, 64, 96, 128, 192,
- * 256, 384, 512} and the boxes 48x32x32, 64x32x32 and 192x128x128.
+ * 256, 384, 512} and the boxes 48x32x32, 64x32x32, 192x128x128, 1152x32x32 and
+ * 1152x768x768.
  * nu: kinematic viscosity; eta: penalization constant C_eta (Sec. 2.1);
  * dtype: FLUSI_F32 or FLUSI_F64.  Builds the integer wavenumber and
  * dealiasing tables (kept iff 3|j| < n_a on axis a), FP64 twiddle tables (and
@@ -326,7 +327,9 @@ int flusi_state_init(flusi_plan plan, void* state, const void* u0, double t0);
  * (zeros outside the 2/3 band). */
 int flusi_state_export_uhat(flusi_plan plan, const void* state, void* uhat);
 
-/* Physical velocity u [3][n][n][nx] of a state. */
+/* Physical velocity u [3][n][n][nx] of a state.  u also holds partly transformed
+ * spectra until the call's last launch; the plan's scratch (three full-layout
+ * spectra) is allocated on first use. */
 int flusi_state_velocity(flusi_plan plan, const void* state, void* u);
 
 /* Time and step count of a state (synchronous). */
@@ -379,15 +382,17 @@ int flusi_pass_times(flusi_plan plan, double* ms, long long* launches);
  * Each stepping pass (y-inverse, x-pass, y-forward, z-pass) exists in three
  * tile variants, 0, 1 and 2 (y passes: columns per workgroup, usually 16, twice
  * or half as many; x-pass: wavefronts of rows per workgroup, two, four or one,
- * and on rows of 1024 points or more its rows; z-pass: columns per workgroup or,
- * on grids below 192, threads per column).  A new plan holds a schedule chosen
- * for its grid and type.  The
+ * and on rows of 1024 points or more its rows; z-pass: columns per workgroup from
+ * 192 to 512 points, threads per column on other grids and always with the sponge
+ * and RK4).  A new plan holds a schedule chosen for its grid and type.  The
  * z-pass runs either as one launch (update, curl and inverse z) or as two
- * (update, then curl + inverse z), with the vorticity sponge always as two from
- * 192 points on.  The velocity field does not depend on
- * the schedule (every variant performs the same operations per value); the
- * x-pass variant changes only the summation order of the FP64 diagnostic
- * integrals (energy, force, torque), at round-off level.
+ * (update, then curl + inverse z); with the vorticity sponge always as two from
+ * 192 points on, with RK4 always as one.  The velocity field depends neither on the
+ * schedule (every variant performs the same operations per value) nor on the calls
+ * that its steps come in; the x-pass variant changes only the summation order of
+ * the FP64 diagnostic integrals (energy, force, torque), at round-off level.  Rows
+ * of 1024 points or more are the exception: x-pass variants 1 and 2 transform a
+ * row's N_z by itself there and agree with variant 0 to rounding.
  * ------------------------------------------------------------------------ */
 typedef struct {
     int y_inverse;   /* tile variant, 0, 1 or 2 */

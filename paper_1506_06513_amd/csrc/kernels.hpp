@@ -103,6 +103,9 @@ __host__ __device__ constexpr int round_up(int a, int b) { return (a + b - 1) / 
 // First-level reduction workgroups per member: every z-pass workgroup reads
 // their NV-value records, so small grids use few; large grids (many x-pass
 // records) use more so that the first level stays shorter than the y-forward.
+// One per 128 groups of rows_x rows, whatever the x-pass's kernel and variant:
+// the count fixes the order of the sums.  (The row kernel leaves fewer records, at
+// 256^3 FP32 8192 where tiles of rows_x rows would leave 16384.)
 __host__ __device__ constexpr int nred_of(int NX, int N) {
     const int n = N * N / rows_x(NX) / 128;
     return n < 16 ? 16 : (n > NRED_MAX ? NRED_MAX : n);
@@ -645,7 +648,8 @@ __host__ __device__ constexpr int xpass_threads() {
 // rows per workgroup also for the sponge's P = 1, since every member of a launch
 // has the same workgroup count), fewer where the rows do not divide; two have
 // less to wait for at the end than four (insect, 4 / 2 / 1: 256^3 FP32 152 / 140 /
-// 136 us, FP64 249 / 227 / 234; 512^3 FP32 988 / 932 / 1036).  Small grids
+// 136 us, FP64 249 / 227 / 234; 512^3 FP32 988 / 932 / 1036: one is ahead only in the
+// first, which the autotuner finds).  Small grids
 // (xrow_share) instead spread over the CUs, and the wavefronts of a workgroup,
 // four with a body, take the points near it together: there one wavefront's chain
 // of mask evaluations would be the length of the kernel.
@@ -702,7 +706,9 @@ __host__ __device__ constexpr int xpass_waves() {
 // chi is 0; rows 2..4 and 5..7: the coordinates of the wings' frames about their
 // outlines' centres (an ellipse's delta exceeds thr where |e_x| > A + thr, as
 // the overshoot beyond the outline along the ray from the centre is at least
-// its x component).  The half-widths carry a margin far above the rounding.
+// its x component).  The half-widths carry a margin far above the rounding.  By
+// selects: as branches on the axis the compiler (ROCm 7.2) made them a switch whose
+// third way lost its value.
 constexpr int MASK_FRAMES = 8;
 template <typename T>
 __device__ __forceinline__ void mask_frames(const KinT<T>& k, T side, T* aff, int r) {
@@ -770,10 +776,11 @@ __device__ __forceinline__ unsigned mask_candidates(const KinT<T>& k, const T* a
 
 // The x-pass of rows held in registers (xr_fft).  R wavefronts with rows, W in all
 // (those beyond R only evaluate the mask).
-// Bound: at large grids the vector units and the waves' latency (65536 rows of
-// 256 points: 690 VALU instructions per row against 1050 of LDS column tiles, and
-// no workgroup barrier between the stages), with the traffic not far below (411
-// MB at 256^3 FP32, 86 us at the rate of a large copy).  Measured per launch, LDS
+// Bound: at large grids the vector units and the waves' latency (256^3
+// FP32 insect, per row: 740 VALU and 66 LDS instructions against 1050 and 106 of LDS
+// column tiles, and no workgroup barrier between the stages), with the traffic not
+// far below (408 MB, 86 us at the rate of a large copy; some 35 MB more are written,
+// where six to eight registers of the three-colour FP32 kernel spill).  Measured per launch, LDS
 // column tiles -> this: 256^3 without a body FP32 168 -> 121 us, FP64 328 -> 224;
 // insect FP32 182 -> 147, FP64 343 -> 251; 512^3 insect FP32 1539 -> 1004; 192^3
 // insect FP64 202 -> 135; 128^3 insect FP32 34.9 -> 24.0, FP64 50.4 -> 36.0, with

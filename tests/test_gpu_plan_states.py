@@ -57,3 +57,28 @@ def test_states_of_one_plan_do_not_mix(between, body, dtype):
         u, t = _solo(seed, ins, dtype, calls)
         assert torch.equal(P.uhat(st), u)
         assert P.time(st) == t
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("body", [None, "sphere", "insect"])
+def test_captured_step_replays_among_steps_of_another_state(body, dtype):
+    # every replay brings its own launch record, whatever the plan was used for since
+    ins = {None: None, "sphere": W.sphere_body(L), "insect": W.model_insect(N, L)}[body]
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        P = F.Plan(N, L, NU, ETA, dtype)
+        a, b = P.new_state(_u0(1)), P.new_state(_u0(2))
+        P.step(a, 1, ins, **CTL)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            P.step(a, 3, ins, **CTL)
+        for _ in range(3):
+            g.replay()
+            P.step(b, 1, ins, **CTL)
+            s.synchronize()
+        u, t, ub = P.uhat(a), P.time(a), P.uhat(b)
+    torch.cuda.synchronize()
+    ua, ta = _solo(1, ins, dtype, (1, 3, 3, 3))
+    assert torch.equal(u, ua) and t == ta
+    assert torch.equal(ub, _solo(2, ins, dtype, (1, 1, 1))[0])
