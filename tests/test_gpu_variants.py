@@ -59,3 +59,24 @@ def test_variants_agree_and_match_64_bits(n, dtype, body, sponge, integrator):
     ex = cases.exact(case, 5)["velocity"]
     err = float((ref.double() - ex).norm() / ex.norm())
     assert err <= (1e-11 if dtype == "f64" else 2e-5), err
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_mixed_members_at_192_equal_their_solo_runs(graph):
+    # one size group with and without the sponge (its members' steps are two z launches),
+    # and one of Runge-Kutta members
+    import paper_1506_06513_amd as fl
+    kinds = [("sphere", True, "ab2"), ("insect", False, "ab2"), ("insect", True, "ab2"), ("sphere", False, "rk4")]
+    runs = [[cases.prepare(dict(kind="solve", nx=192, n=192, dtype="f32", body=b, steps=4, integrator=i, sponge=sp,
+                                flow="inflow"), 7 + j) for j, (b, sp, i) in enumerate(kinds)] for _ in range(2)]
+    ens = fl.Ensemble("f32")
+    for s in runs[0]:
+        ens.add(s["plan"], s["st"], s["p"]["insect"], **s["p"]["controls"])
+    for _ in range(2):
+        ens.step(2, graph=graph)
+        torch.cuda.synchronize()
+    for a, b in zip(*runs):
+        b["plan"].step(b["st"], 4, b["p"]["insect"], **b["p"]["controls"])
+        assert torch.equal(a["plan"].velocity(a["st"]), b["plan"].velocity(b["st"]))
+        assert a["plan"].time(a["st"]) == b["plan"].time(b["st"])
+    ens.close()
